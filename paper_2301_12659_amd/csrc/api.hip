@@ -93,6 +93,7 @@ struct Layout {
   size_t xseq;  // count of xn's workgroups done (md_newton_steps)
   size_t mseq;  // count of M's columns done (md_newton_steps)
   size_t rs;    // rows of R scaled by their diagonal (back substitution of M)
+  size_t need;  // whether M needs the factorization (launch_inverse)
   size_t total;
 };
 
@@ -135,6 +136,7 @@ Layout newton_layout(const md_plan *p) {
   w.xseq = take(1);
   w.mseq = take(1);
   w.rs = take(L * n * n);
+  w.need = take(1);
   w.total = off;
   return w;
 }
@@ -166,7 +168,7 @@ mdk::QrPrep qr_prep(int L, int n, void *scratch) {
 // prepared: the LDS QR's hand-over memory was prepared by an earlier launch
 // on this stream (qr_prep).
 hipError_t run_qr(int L, int n, double *a, double *tau, double *qt, int32_t *status, void *scratch, hipStream_t st,
-                  bool prepared = false) {
+                  bool prepared = false, const int *need = nullptr) {
   char *p = static_cast<char *>(scratch);
   int *flags = reinterpret_cast<int *>(p);
   p += align_up((size_t)n * sizeof(int));
@@ -176,8 +178,8 @@ hipError_t run_qr(int L, int n, double *a, double *tau, double *qt, int32_t *sta
   p += align_up((size_t)n * 2 * L * sizeof(double));
   unsigned *bar = reinterpret_cast<unsigned *>(p);
   if (mdk::qr_lds_workgroups(L, n, qt != nullptr) > 0)
-    return mdk::launch_qr_lds(L, n, a, tau, qt, status, flags, vboard, tboard, st, prepared);
-  return mdk::launch_qr(L, n, a, tau, qt, status, bar, st);
+    return mdk::launch_qr_lds(L, n, a, tau, qt, status, flags, vboard, tboard, st, prepared, need);
+  return mdk::launch_qr(L, n, a, tau, qt, status, bar, st, need);
 }
 
 // Scratch of md_qr_noalloc: the QR's flags, reflector board and scalar slots in a static
@@ -207,8 +209,11 @@ int noalloc_scratch(void **out) {
   return MD_OK;
 }
 
-int series_solve_impl(int L, int n, int D, const double *qr, const double *tau, const double *A, double *rhs_dx,
-                      void *ws, hipStream_t st, int32_t *status) {
+// The staged solve from M = R^{-1} Q^T of the QR factors.  With need
+// (nullable) qr holds A_0 itself: M by refinement, else (*need, decided on the
+// device) by the factorization, in place, with its scratch in qrs.
+int series_solve_impl(int L, int n, int D, double *qr, double *tau, const double *A, double *rhs_dx, void *ws,
+                      hipStream_t st, int32_t *status, int *need = nullptr, void *qrs = nullptr) {
   size_t off = 0;
   auto take = [&](size_t doubles) {
     double *p = at(ws, off);
@@ -220,9 +225,14 @@ int series_solve_impl(int L, int n, int D, const double *qr, const double *tau, 
   double *At = take((size_t)L * nn * D), *rT = take((size_t)L * nD), *dxT = take((size_t)L * nD);
   int *sync = reinterpret_cast<int *>(take(mdk::stages_sync_ints(D) / 2 + 1));
   hipError_t e;
+  if (need) {
+    Timed t(MD_CLASS_QR, st);
+    if ((e = mdk::launch_inverse(L, n, qr, N, M, need, st)) != hipSuccess) return hip_fail(e, "inverse");
+    if ((e = run_qr(L, n, qr, tau, nullptr, status, qrs, st, false, need)) != hipSuccess) return hip_fail(e, "qr");
+  }
   {
     Timed t(MD_CLASS_QHB_BS, st);
-    if ((e = mdk::launch_form_m(L, n, qr, tau, invd, M, status, st)) != hipSuccess) return hip_fail(e, "form M");
+    if ((e = mdk::launch_form_m(L, n, qr, tau, invd, M, status, st, need)) != hipSuccess) return hip_fail(e, "form M");
   }
   {
     Timed t(MD_CLASS_UPDATES, st);
@@ -494,7 +504,9 @@ int md_series_solve(int prec, int n, int d, const double *qr, const double *tau,
     return fail(MD_EINVAL, "bad precision, dimension or degree");
   if (!qr || !tau || !rhs_dx || (d > 0 && !A)) return fail(MD_EINVAL, "NULL argument");
   if (!ws || ws_bytes < solve_bytes(prec, n, d + 1)) return fail(MD_ENOSPACE, "workspace too small");
-  return series_solve_impl(prec, n, d + 1, qr, tau, A, rhs_dx, ws, st, dev_status);
+  // (the factors are only read)
+  return series_solve_impl(prec, n, d + 1, const_cast<double *>(qr), const_cast<double *>(tau), A, rhs_dx, ws, st,
+                           dev_status);
 }
 
 // One Newton step with the residual b = -p(x) at the plan's precision L and
@@ -544,17 +556,24 @@ static int newton_step_impl(const md_plan *p, int Ls, int lo, int hi, bool keep_
                                        qr_prep(Ls, n, at(ws, w.bar)))) != hipSuccess)
         return hip_fail(e, "A_0 assembly");
     }
-    // 2. fork: QR of A_0 with Q^T, then M = R^{-1} Q^T, on the second stream
+    // 2. fork: M = A_0^{-1} on the second stream, by refinement where that is
+    //    as good as the factorization; else (decided on the device) the QR of
+    //    A_0 with Q^T and M = R^{-1} Q^T
     if ((e = hipEventRecord(p->fork, st)) != hipSuccess) return hip_fail(e, "fork");
     if ((e = hipStreamWaitEvent(p->aux, p->fork, 0)) != hipSuccess) return hip_fail(e, "fork wait");
+    int *need = mdk::inverse_refined(Ls, n) ? reinterpret_cast<int *>(at(ws, w.need)) : nullptr;
     {
       Timed t(MD_CLASS_QR, p->aux);
-      if ((e = run_qr(Ls, n, qr, tau, qt, dev_status, at(ws, w.bar), p->aux, true)) != hipSuccess)
+      // (the inverse in doubles lies where Q^T would)
+      if (need && (e = mdk::launch_inverse(Ls, n, qr, qt, M, need, p->aux)) != hipSuccess)
+        return hip_fail(e, "inverse");
+      if ((e = run_qr(Ls, n, qr, tau, qt, dev_status, at(ws, w.bar), p->aux, true, need)) != hipSuccess)
         return hip_fail(e, "qr");
     }
     {
       Timed t(MD_CLASS_QHB_BS, p->aux);
-      if ((e = mdk::launch_m_from_qt(Ls, n, qr, qt, invd, M, dev_status, p->aux, at(ws, w.rs))) != hipSuccess)
+      if ((e = mdk::launch_m_from_qt(Ls, n, qr, qt, invd, M, dev_status, p->aux, at(ws, w.rs), nullptr, need)) !=
+          hipSuccess)
         return hip_fail(e, "M");
     }
     if ((e = hipEventRecord(p->join, p->aux)) != hipSuccess) return hip_fail(e, "join");
@@ -664,6 +683,7 @@ static int newton_steps_impl(const md_plan *p, int count, const double *cff, con
   int *xseq = reinterpret_cast<int *>(at(ws, w.xseq)), *mseq = reinterpret_cast<int *>(at(ws, w.mseq));
   // M counted on the device only where the small back substitution forms it
   const bool mcount = n <= 64;
+  int *need = mdk::inverse_refined(L, n) ? reinterpret_cast<int *>(at(ws, w.need)) : nullptr;
   if ((e = mdk::launch_status_init(dev_status, st, xseq, mseq)) != hipSuccess) return hip_fail(e, "status");
   double *b = at(ws, w.b), *A = at(ws, w.A), *r = at(ws, w.r), *dx = at(ws, w.dx), *N = at(ws, w.N);
   double *At = at(ws, w.At), *dxT = at(ws, w.dxT), *invd = at(ws, w.invd), *xn = at(ws, w.xn);
@@ -703,13 +723,15 @@ static int newton_steps_impl(const md_plan *p, int count, const double *cff, con
       if ((e = mdk::launch_assemble_A0(L, n, 1, p->nnz, p->d_asm_ptr, p->d_asm_ent, a.der, qrs[k], p->aux,
                                        qr_prep(L, n, at(ws, w.bar)))) != hipSuccess)
         return hip_fail(e, "A_0 assembly");
-      if ((e = run_qr(L, n, qrs[k], taus[k], qts[k], dev_status, at(ws, w.bar), p->aux, true)) != hipSuccess)
+      if (need && (e = mdk::launch_inverse(L, n, qrs[k], qts[k], Ms[k], need, p->aux)) != hipSuccess)
+        return hip_fail(e, "inverse");
+      if ((e = run_qr(L, n, qrs[k], taus[k], qts[k], dev_status, at(ws, w.bar), p->aux, true, need)) != hipSuccess)
         return hip_fail(e, "qr");
     }
     {
       Timed t(MD_CLASS_QHB_BS, p->aux);
       if ((e = mdk::launch_m_from_qt(L, n, qrs[k], qts[k], invd, Ms[k], dev_status, p->aux, at(ws, w.rs),
-                                     mcount ? mseq : nullptr)) != hipSuccess)
+                                     mcount ? mseq : nullptr, need)) != hipSuccess)
         return hip_fail(e, "M");
     }
     if ((last || !mcount) && (e = hipEventRecord(p->join, p->aux)) != hipSuccess) return hip_fail(e, "join");
@@ -899,7 +921,7 @@ int md_step_arrays(const md_plan *p, void *ws, size_t ws_bytes, double **b, doub
 // series, b and A, the real form of the block system (2n) with its QR and the
 // real staged-solve workspace, dx, and the norms of the imaginary parts.
 struct CLayout {
-  size_t val, der, b, A, At, bt, a0, tau, qrs, solve, dx, nt, total;
+  size_t val, der, b, A, At, bt, a0, tau, qrs, solve, dx, nt, need, total;
 };
 
 static CLayout complex_layout(const md_plan *p) {
@@ -924,6 +946,7 @@ static CLayout complex_layout(const md_plan *p) {
   w.solve = take(solve_bytes((int)L, (int)N, (int)D));
   w.dx = take(2 * L * n * D * d8);
   w.nt = take(2 * D * d8);
+  w.need = take(d8);
   w.total = off;
   return w;
 }
@@ -1000,11 +1023,14 @@ int md_newton_step_complex(const md_plan *p, const double *cff, const double *cs
     if ((e = mdk::launch_complex_embed(L, n, D, A, b, At, bt, st)) != hipSuccess) return hip_fail(e, "real form");
     if ((e = mdk::launch_extract(L, N, D, 0, At, a0, st)) != hipSuccess) return hip_fail(e, "A_0");
   }
-  {
+  int *need = mdk::inverse_refined(L, N) ? reinterpret_cast<int *>(at(ws, w.need)) : nullptr;
+  if (!need) {
     Timed t(MD_CLASS_QR, st);
     if ((e = run_qr(L, N, a0, tau, nullptr, dev_status, at(ws, w.qrs), st)) != hipSuccess) return hip_fail(e, "qr");
   }
-  if ((rc = series_solve_impl(L, N, D, a0, tau, At, bt, at(ws, w.solve), st, dev_status)) != MD_OK) return rc;
+  if ((rc = series_solve_impl(L, N, D, a0, tau, At, bt, at(ws, w.solve), st, dev_status, need, at(ws, w.qrs))) !=
+      MD_OK)
+    return rc;
   {
     Timed t(MD_CLASS_X_UPDATE, st);
     if ((e = mdk::launch_complex_unpack(L, n, D, bt, dx, st)) != hipSuccess) return hip_fail(e, "dx");

@@ -329,6 +329,26 @@ def gen_fma_lazy(L):
     return E, u
 
 
+def gen_fma_lazy_h(L):
+    """fma_lazy with an operand a of L - 1 limbs (a's products of level L - 1
+    and above with b's L limbs included)."""
+    E = Emitter()
+    a = [f"a[{i}]" for i in range(L - 1)]
+    b = [f"b[{i}]" for i in range(L)]
+    terms, last = [[] for _ in range(L)], []
+    for p in range(L - 1):
+        for q in range(L - p):
+            if p + q < L - 1:
+                hi, lo = E.two_prod(a[p], b[q])
+                terms[p + q].append(hi)
+                terms[p + q + 1].append(lo)
+            else:
+                last.append((a[p], b[q]))
+    for g in range(L):
+        terms[g].insert(0, f"u[{g}]")
+    return E, level_sums(E, L, terms, last)
+
+
 def gen_add_lazy(L):
     """u := u + w for two accumulators of level sums (no renormalization):
     the step of a reduction tree over lazily accumulated partial sums."""
@@ -367,7 +387,9 @@ def generate(counts=None):
     out.append("// Multiple-double routines for L = 1, 2, 4, 8 limbs (see gen_md.py for the scheme; one limb is")
     out.append("// plain double arithmetic, the paper's D precision).")
     out.append("")
-    for L in (1, 2, 4, 8):
+    # 3, 5 and 9 limbs: what a residual with one limb beyond a precision's
+    # own takes (the refinement of the inverse of A_0)
+    for L in (1, 2, 3, 4, 5, 8, 9):
         out.append(f"template <> struct MD<{L}> {{")
         out.append(f"  static constexpr int L = {L};")
         defs = [
@@ -384,6 +406,10 @@ def generate(counts=None):
             ("add_lazy", "double (&u)[L], const double (&w)[L]", gen_add_lazy(L), "u"),
             ("renorm", "const double (&x)[L], double (&r)[L]", gen_renorm(L), "r"),
         ]
+        if L in (3, 5, 9):
+            defs = [d for d in defs if d[0] in ("add", "add_lazy", "renorm")]
+            defs.append(("fma_lazy_h", "double (&u)[L], const double (&a)[L - 1], const double (&b)[L]",
+                         gen_fma_lazy_h(L), "u"))
         for name, sig, (E, r), outname in defs:
             if counts is not None:
                 counts.setdefault(str(L), {})[name] = {"instr": E.instr, "flops": E.flops}

@@ -79,21 +79,27 @@ hipError_t launch_assemble_A0(int L, int n, int D, int nnz, const int32_t *asm_p
 // linalg.hip
 // and *counter = *counter2 = 0
 hipError_t launch_status_init(int32_t *status, hipStream_t st, int *counter = nullptr, int *counter2 = nullptr);
+// need (nullable, here and in the launches below): a word in device memory,
+// set by an earlier launch on st (launch_inverse); the kernels return at once
+// when it is 0.
 hipError_t launch_qr(int L, int n, double *a, double *tau, double *qt, int32_t *status, unsigned *bar,
-                     hipStream_t st);
+                     hipStream_t st, const int *need = nullptr);
 int qr_lds_workgroups(int L, int n, bool with_qt);
 // prepared: the hand-over memory (flags, tboard) was prepared by an earlier
 // launch on st (QrPrep).
 hipError_t launch_qr_lds(int L, int n, double *a, double *tau, double *qt, int32_t *status, int *flags,
-                         double *vboard, double *tboard, hipStream_t st, bool prepared = false);
+                         double *vboard, double *tboard, hipStream_t st, bool prepared = false,
+                         const int *need = nullptr);
 // rs (nullable): L n n doubles of scratch for the rows of R scaled by their
 // diagonal (n <= 64: a back substitution whose steps have no division)
 // done (nullable, with rs): each column's workgroup adds one to it after
-// agent-scope stores and a wait for them
+// agent-scope stores and a wait for them (when *need is 0: at once, M being
+// complete since an earlier launch)
 hipError_t launch_m_from_qt(int L, int n, const double *qr, const double *qt, double *invd, double *M,
-                            int32_t *status, hipStream_t st, double *rs = nullptr, int *done = nullptr);
+                            int32_t *status, hipStream_t st, double *rs = nullptr, int *done = nullptr,
+                            const int *need = nullptr);
 hipError_t launch_form_m(int L, int n, const double *qr, const double *tau, double *invd, double *M, int32_t *status,
-                         hipStream_t st);
+                         hipStream_t st, const int *need = nullptr);
 hipError_t launch_extract(int L, int n, int D, int k, const double *A, double *out, hipStream_t st);
 hipError_t launch_transpose(int L, const double *in, double *out, size_t rows, int cols, size_t in_ls,
                             size_t out_ls, hipStream_t st);
@@ -151,6 +157,13 @@ hipError_t launch_complex_embed(int L, int n, int D, const double *A, const doub
 // dx [2][L][n][D] from dxt [L][2n][D].
 hipError_t launch_complex_unpack(int L, int n, int D, const double *dxt, double *dx, hipStream_t st);
 hipError_t launch_max(int count, const double *b, double *a, hipStream_t st);
+
+// inverse.hip: M = a^{-1} by refinement from the inverse of a's leading limbs
+// in doubles (x0 [n][n] scratch), where inverse_refined(); *need becomes 1
+// where that is not as good as a factorization (M is then not complete), else
+// 0.
+bool inverse_refined(int L, int n);
+hipError_t launch_inverse(int L, int n, const double *a, double *x0, double *M, int *need, hipStream_t st);
 
 // residual.hip: r [L][nrows][D] = b - T dx on rows (NULL: all), norm1 [D] (nullable).
 hipError_t launch_residual(int L, int n, int D, int nrows, const int32_t *rows, const double *A, const double *b,

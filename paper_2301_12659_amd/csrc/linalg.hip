@@ -105,7 +105,8 @@ __global__ void zero_u32_kernel(unsigned *p) {
 // barrier per column makes the updated column c+1 visible to all.
 template <int L>
 __global__ void __launch_bounds__(256) qr_kernel(int n, double *a, double *tau, double *qt, int32_t *status,
-                                                 unsigned *bar) {
+                                                 unsigned *bar, const int *need) {
+  if (need && *need == 0) return;
   extern __shared__ double vsh[];  // the current reflector v, [L][n]
   __shared__ double red[4][L];
   __shared__ double sh_tau[L], sh_inv[L], sh_beta[L];
@@ -295,8 +296,9 @@ constexpr int QR_GROUP = 2;
 // below it for the A_0 part; Q^T for the identity part.
 template <int L>
 __global__ void __launch_bounds__(256) qr_lds_kernel(int n, double *a, double *tau, double *qt, int32_t *status,
-                                                     int *flags, double *vboard, double *tboard) {
+                                                     int *flags, double *vboard, double *tboard, const int *need) {
   extern __shared__ double lds[];
+  if (need && *need == 0) return;
   // this launch runs beside the evaluation kernel and is on the critical
   // path: its wavefronts get the highest issue priority on a shared CU
   __builtin_amdgcn_s_setprio(3);
@@ -590,7 +592,8 @@ __global__ void zero_i32_kernel(int *p, int count) {
 // n * 2^(-53 L) times the largest one (leading limbs) means A_0 is singular to
 // working precision; it is reported and its inverse set to zero.
 template <int L>
-__global__ void invdiag_kernel(int n, const double *qr, double *invd, int32_t *status) {
+__global__ void invdiag_kernel(int n, const double *qr, double *invd, int32_t *status, const int *need) {
+  if (need && *need == 0) return;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const size_t nn = (size_t)n * n;
@@ -643,7 +646,8 @@ __device__ void back_subst(int n, const double *qr, const double *invd, double *
 // column, y kept in LDS.
 template <int L>
 __global__ void __launch_bounds__(64, 1) form_m_kernel(int n, const double *qr, const double *tau, const double *invd,
-                                                    double *M) {
+                                                    double *M, const int *need) {
+  if (need && *need == 0) return;
   extern __shared__ double y[];  // [L][n]
   const int c = blockIdx.x, lane = threadIdx.x;
   const size_t nn = (size_t)n * n;
@@ -703,7 +707,8 @@ __global__ void __launch_bounds__(64, 1) form_m_kernel(int n, const double *qr, 
 // augmented part): one wavefront per column.
 template <int L>
 __global__ void __launch_bounds__(64, 1) m_from_qt_kernel(int n, const double *qr, const double *qt, const double *invd,
-                                                       double *M) {
+                                                       double *M, const int *need) {
+  if (need && *need == 0) return;
   extern __shared__ double y[];  // [L][n]
   const int c = blockIdx.x, lane = threadIdx.x;
   const size_t nn = (size_t)n * n;
@@ -737,7 +742,9 @@ __device__ __forceinline__ double read_lane(double x, int i) {
 // times the largest one (leading limbs) means A_0 is singular to working
 // precision: MD_ESINGULAR, and the row's 1 / R_pp is zero.
 template <int L>
-__global__ void __launch_bounds__(64) rscale_kernel(int n, const double *qr, double *rs, double *dq, int32_t *status) {
+__global__ void __launch_bounds__(64) rscale_kernel(int n, const double *qr, double *rs, double *dq, int32_t *status,
+                                                    const int *need) {
+  if (need && *need == 0) return;
   const int p = blockIdx.x, lane = threadIdx.x;
   const size_t nn = (size_t)n * n;
   double rmax = 0.0;
@@ -773,7 +780,12 @@ __global__ void __launch_bounds__(64) rscale_kernel(int n, const double *qr, dou
 // from memory, not the L2).
 template <int L>
 __global__ void __launch_bounds__(64, 1) m_from_qt_small_kernel(int n, const double *rs, const double *dq,
-                                                             const double *qt, double *M, int *done) {
+                                                             const double *qt, double *M, int *done,
+                                                             const int *need) {
+  if (need && *need == 0) {  // M was formed by an earlier launch on this stream
+    if (done && threadIdx.x == 0) __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return;
+  }
   // raised wave priority: the kernel runs beside the evaluation, whose
   // wavefronts fill the CUs (M beside it: 47 against 180 us)
   __builtin_amdgcn_s_setprio(3);
@@ -1578,7 +1590,7 @@ static void allow_large_lds(K kernel) {
 }
 
 hipError_t launch_qr(int L, int n, double *a, double *tau, double *qt, int32_t *status, unsigned *bar,
-                     hipStream_t st) {
+                     hipStream_t st, const int *need) {
   const int G = qr_workgroups(n, qt != nullptr);
   hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(64), 0, st, bar);
   MD_DISPATCH(L, {
@@ -1588,7 +1600,7 @@ hipError_t launch_qr(int L, int n, double *a, double *tau, double *qt, int32_t *
       attr = true;
     }
     hipLaunchKernelGGL(qr_kernel<LL>, dim3(G), dim3(256), (size_t)LL * n * sizeof(double), st, n, a, tau, qt, status,
-                       bar);
+                       bar, need);
   });
   return hipGetLastError();
 }
@@ -1618,7 +1630,7 @@ size_t qr_lds_bytes(int L, int n, int G, bool with_qt) {
 }
 
 hipError_t launch_qr_lds(int L, int n, double *a, double *tau, double *qt, int32_t *status, int *flags,
-                         double *vboard, double *tboard, hipStream_t st, bool prepared) {
+                         double *vboard, double *tboard, hipStream_t st, bool prepared, const int *need) {
   const int G = qr_lds_workgroups(L, n, qt != nullptr);
   if (G == 0) return hipErrorInvalidValue;
   const size_t lds = qr_lds_bytes(L, n, G, qt != nullptr);
@@ -1639,18 +1651,19 @@ hipError_t launch_qr_lds(int L, int n, double *a, double *tau, double *qt, int32
       (void)hipGetLastError();
       attr = true;
     }
-    hipLaunchKernelGGL(qr_lds_kernel<LL>, dim3(G), dim3(256), lds, st, n, a, tau, qt, status, flags, vboard, tboard);
+    hipLaunchKernelGGL(qr_lds_kernel<LL>, dim3(G), dim3(256), lds, st, n, a, tau, qt, status, flags, vboard, tboard,
+                       need);
   });
   return hipGetLastError();
 }
 
 hipError_t launch_m_from_qt(int L, int n, const double *qr, const double *qt, double *invd, double *M,
-                            int32_t *status, hipStream_t st, double *rs, int *done) {
+                            int32_t *status, hipStream_t st, double *rs, int *done, const int *need) {
   if (n <= 64 && rs) {
     MD_DISPATCH(L, {
-      hipLaunchKernelGGL(rscale_kernel<LL>, dim3(n), dim3(64), 0, st, n, qr, rs, invd, status);
+      hipLaunchKernelGGL(rscale_kernel<LL>, dim3(n), dim3(64), 0, st, n, qr, rs, invd, status, need);
       hipLaunchKernelGGL(m_from_qt_small_kernel<LL>, dim3(n), dim3(64), 0, st, n, (const double *)rs,
-                         (const double *)invd, qt, M, done);
+                         (const double *)invd, qt, M, done, need);
     });
     return hipGetLastError();
   }
@@ -1660,24 +1673,24 @@ hipError_t launch_m_from_qt(int L, int n, const double *qr, const double *qt, do
       allow_large_lds(m_from_qt_kernel<LL>);
       attr = true;
     }
-    hipLaunchKernelGGL(invdiag_kernel<LL>, dim3((n + 63) / 64), dim3(64), 0, st, n, qr, invd, status);
+    hipLaunchKernelGGL(invdiag_kernel<LL>, dim3((n + 63) / 64), dim3(64), 0, st, n, qr, invd, status, need);
     hipLaunchKernelGGL(m_from_qt_kernel<LL>, dim3(n), dim3(64), (size_t)LL * n * sizeof(double), st, n, qr, qt,
-                       (const double *)invd, M);
+                       (const double *)invd, M, need);
   });
   return hipGetLastError();
 }
 
 hipError_t launch_form_m(int L, int n, const double *qr, const double *tau, double *invd, double *M, int32_t *status,
-                         hipStream_t st) {
+                         hipStream_t st, const int *need) {
   MD_DISPATCH(L, {
     static bool attr = false;
     if (!attr) {
       allow_large_lds(form_m_kernel<LL>);
       attr = true;
     }
-    hipLaunchKernelGGL(invdiag_kernel<LL>, dim3((n + 63) / 64), dim3(64), 0, st, n, qr, invd, status);
+    hipLaunchKernelGGL(invdiag_kernel<LL>, dim3((n + 63) / 64), dim3(64), 0, st, n, qr, invd, status, need);
     hipLaunchKernelGGL(form_m_kernel<LL>, dim3(n), dim3(64), (size_t)LL * n * sizeof(double), st, n, qr, tau,
-                       (const double *)invd, M);
+                       (const double *)invd, M, need);
   });
   return hipGetLastError();
 }
