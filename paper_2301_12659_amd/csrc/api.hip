@@ -589,13 +589,15 @@ static int newton_step_impl(const md_plan *p, int Ls, int lo, int hi, bool keep_
   int *sync = reinterpret_cast<int *>(at(ws, w.sync));
   const mdk::TOut rt{r, lo, W, Ls}, atT{At, 0, W, Ls};
   const int nsync = mdk::stages_sync_ints(W);
+  // (a refined M leaves the QR to the matrices that need it)
+  const bool beside_qr = !keep_m && !mdk::inverse_refined(Ls, n);
   const size_t ndx = (size_t)Ls * n * W;
   if (!mixed) {
-    int rc = eval_diff_impl(p, hi, cff, cst, x, b, A, ws, st, tsz, !keep_m, rt, atT, sync, nsync, dxT, ndx);
+    int rc = eval_diff_impl(p, hi, cff, cst, x, b, A, ws, st, tsz, beside_qr, rt, atT, sync, nsync, dxT, ndx);
     if (rc != MD_OK) return rc;
   } else {
     eval_args(p, cff, x, ws, hi, a);
-    a.beside_qr = keep_m ? 0 : 1;
+    a.beside_qr = beside_qr ? 1 : 0;
     a.values_only = 1;
     if (tsz) a.vsize = at(ws, w.vsz);
     {

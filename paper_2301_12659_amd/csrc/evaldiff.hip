@@ -351,6 +351,7 @@ hipError_t launch_evaldiff_T(const EvalArgs &a, int maxexp, double *pw_mut, hipS
     const int blocks = (a.n + wpb - 1) / wpb;
     hipLaunchKernelGGL(power_kernel<L>, dim3(blocks), dim3(256), lds, st, a.n, a.D, a.Dc, maxexp - 1, a.x, pw_mut);
   }
+  if (evaldiff_on_digits(L, a.Dc)) return launch_evaldiff_digits(L, a, st);
   if (a.m > 0) {
     if (G == 64 && !a.beside_qr) {  // two wavefronts per monomial
       hipLaunchKernelGGL(evaldiff_pair_kernel<L>, dim3(a.m), dim3(128), (size_t)6 * L * (a.Dc + 1) * sizeof(double),

@@ -31,6 +31,10 @@ __device__ __forceinline__ void qr_prep_item(const QrPrep &q, size_t t) {
 
 // evaldiff.hip
 hipError_t launch_evaldiff(int L, const EvalArgs &a, int maxexp, double *pw, hipStream_t st);
+// evaldigits.hip: the same products on digits, where evaldiff_on_digits()
+// (launch_evaldiff takes it there; a.pw as launch_evaldiff leaves it).
+bool evaldiff_on_digits(int L, int Dc);
+hipError_t launch_evaldiff_digits(int L, const EvalArgs &a, hipStream_t st);
 // Coefficient 0 of the derivative products only (der[.][.][0]), one thread
 // per monomial; for plans whose supports have at most
 // evaldiff0_max_support(L) variables (none for octo doubles).
