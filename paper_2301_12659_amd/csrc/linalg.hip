@@ -985,8 +985,8 @@ __device__ __forceinline__ bool wait_geq(const int *ctr, int target, int32_t *st
 
 // Coefficient 0 of the next iterate, x_0 + dx_0 with dx_0 = M r_0, by the
 // operations the persistent staged solve and finish_kernel apply to it: one
-// wavefront per row i, lane v accumulates M(i, v) r_0(v) into zeroed level
-// sums, one 64-lane butterfly of level sums, one renormalization (the first
+// wavefront per row i, lane v accumulates M(i, v) r_0(v) (and columns v + 64,
+// v + 128) into zeroed level sums, one 64-lane butterfly of level sums, one renormalization (the first
 // stage of stages_persistent_kernel), then the addition of finish_kernel.
 // The result is therefore the x_0 that the next step reads, bit for bit,
 // available before the staged solve has run; xn [L][n].  This and the two
@@ -996,12 +996,12 @@ __device__ __forceinline__ void next_x0_block(int n, int D, const double *M, con
                                               double *xn, int *done) {
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int i = blockIdx.x * 4 + wv;
-  const bool row = i < n, col = lane < n;
-  const int ii = row ? i : 0, v = col ? lane : 0;
+  const bool row = i < n;
+  const int ii = row ? i : 0;
   const size_t nn = (size_t)n * n, nD = (size_t)n * D;
   double acc[L], r[L];
   md::zero<L>(acc);
-  if (col) {
+  for (int v = lane; v < n; v += 64) {
     double m[L], a[L];
     ld<L>(M, nn, (size_t)ii * n + v, m);
     ld<L>(rT, nD, (size_t)v, a);
@@ -1049,13 +1049,13 @@ constexpr int SYNC_STRIDE = 64;
 // staged solve takes as a whole: N = M A_1, P = M A_2, Q = M A_3.
 constexpr int STAGE_PRODUCTS = 3;
 
-// The whole staged solve in one launch, for n <= 64.  With P = M A_2 and
+// The whole staged solve in one launch, for n <= 64 C.  With P = M A_2 and
 // Q = M A_3 the recurrence is reassociated twice more,
 //     dx_k = M r''_k - N dx_{k-1} - P dx_{k-2} - Q dx_{k-3},
 //     r''_k = b_k - sum_{j>=4} A_j dx_{k-j},
 // so that a stage only needs right-hand-side terms at least three stages
 // old.  Solver workgroup s (s < Gs = ceil(n/2)) owns rows i = 2 s + w, w = 0, 1,
-// with two wavefronts per row (lane v holds column v):
+// with two wavefronts per row (lane v holds columns v, v + 64, ... of C):
 //   * the critical wavefront of row i keeps N(i,.) in registers; at stage k it
 //     waits for every solver's dx_{k-1}, adds N(i,.) dx_{k-1} to the level
 //     sums pre_k(i) left in LDS by its companion, reduces them over the 64
@@ -1073,9 +1073,9 @@ constexpr int STAGE_PRODUCTS = 3;
 // stores, and a reader polls the entries it needs with agent-scope loads
 // until no limb is empty (no flag, no wait for the stores, one round trip).
 // Updater (g, b) owns the rows 16 b .. 16 b + 15 (one team of 16
-// lanes per row) of coefficient m = 4 + g (and m + Gm when there are more than
-// 64 coefficients from 4 on): in round q, once dx_q is out, every lane adds
-// its four terms of A_{m-q}(i,.) dx_q to level sums kept in registers across
+// lanes per row) of coefficient m = 4 + g, or of two coefficients 4 + 2 g and
+// 5 + 2 g (pairs: one each would take too many workgroups): in round q, once dx_q is out, every lane adds
+// its 4 C terms of A_{m-q}(i,.) dx_q to level sums kept in registers across
 // the rounds; after round m - 4 the team reduces them, renormalizes,
 // stores r''_m(i) = b_m(i) - sum and counts itself done for m, so r''_m is
 // written once, by its owner.  Everything handed between workgroups (dx,
@@ -1083,35 +1083,41 @@ constexpr int STAGE_PRODUCTS = 3;
 // for the stores before its counter), never through fences: a fence would
 // write back or invalidate a whole L2 at every hand-over, hundreds of them
 // per stage.  All
-// workgroups must be resident together; waits are bounded and report
-// MD_EHIP, after which every wavefront of a workgroup leaves at the same
-// barrier.
-template <int L>
-__global__ void __launch_bounds__(256) stages_persistent_kernel(int n, int D, int Gs, int Gm, const double *M,
+// solvers must be resident together; an updater leaves after its last round, in
+// the order of the coefficients, which is the order of dispatch, so that
+// updaters that find no room at first take the places of those that the chain
+// has passed.  Waits are bounded and report MD_EHIP, after which every wavefront
+// of a workgroup leaves at the same barrier.
+template <int L, int C>
+__global__ void __launch_bounds__(256, 3) stages_persistent_kernel(int n, int D, int Gs, int pairs, const double *M,
                                                                 const double *NP, const double *At, double *rT,
                                                                 double *dxT, int *sync, int32_t *status) {
   __shared__ int sh_dead[2];               // a wait of stage k timed out (slot k mod 2)
   __shared__ int sh_ok;                    // an updater round may start
   __shared__ int sh_x1[2];                 // stage k whose dx_{k-1} is in x1s[w]
-  __shared__ double x1s[2][L * 64];        // dx_{k-1}, critical -> companion wavefront of row slot w
+  __shared__ double x1s[2][L * 64 * C];    // dx_{k-1}, critical -> companion wavefront of row slot w
   __shared__ double pres[2][2][L * 64];    // pre_k level sums of row slot w in slot k mod 2
-  __shared__ double xq[L * 64];            // dx_q of an updater round
+  __shared__ double xq[L * 64 * C];        // dx_q of an updater round
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const size_t nn = (size_t)n * n, nD = (size_t)n * D, nnD = nn * D;
   const int Bm = (n + 15) / 16;
   auto rounds = [&](int m) { return sync + (size_t)(2 + m) * SYNC_STRIDE; };
   auto poll = [&](const int *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-  // wavefront-wide poll of dx_k (lane v: dx_k(v), its L limbs) until no limb
-  // is empty; lanes v >= n get zeros.  Bounded: false and MD_EHIP on time-out.
-  auto poll_dx = [&](int k, double (&x)[L]) {
+  // wavefront-wide poll of dx_k (lane v: dx_k of its C columns, L limbs each)
+  // until no limb is empty; columns from n on get zeros.  Bounded: false and
+  // MD_EHIP on time-out.
+  auto poll_dx = [&](int k, double (&x)[C][L]) {
     long spins = 0;
     while (true) {
       bool full = true;
-      md::zero<L>(x);
-      if (lane < n) {
-        ld_agent<L>(dxT, nD, (size_t)k * n + lane, x);
 #pragma unroll
-        for (int l = 0; l < L; ++l) full = full && !slot_empty(x[l]);
+      for (int c = 0; c < C; ++c) {
+        md::zero<L>(x[c]);
+        if (lane + 64 * c < n) {
+          ld_agent<L>(dxT, nD, (size_t)k * n + lane + 64 * c, x[c]);
+#pragma unroll
+          for (int l = 0; l < L; ++l) full = full && !slot_empty(x[c][l]);
+        }
       }
       if (__all(full)) return true;
       __builtin_amdgcn_s_sleep(1);
@@ -1125,34 +1131,42 @@ __global__ void __launch_bounds__(256) stages_persistent_kernel(int n, int D, in
     const int w = wv & 1;              // row slot
     const bool crit = wv < 2;          // critical wavefront (else the companion)
     const int i = blockIdx.x * 2 + w;
-    const bool row = i < n, col = lane < n;
-    const int ii = row ? i : 0, v = col ? lane : 0;
+    const bool row = i < n;
+    const int ii = row ? i : 0;
+    auto col = [&](int c) { return lane + 64 * c < n; };
     if (tid < 2) {
       sh_dead[tid] = 0;
       sh_x1[tid] = 0;
     }
     double *const slot0 = &pres[w][0][0], *const slot1 = &pres[w][1][0];
     if (crit) {
-      double nv[L];
-      md::zero<L>(nv);
-      if (row && col && D > 1) {
-        ld<L>(NP, nn, (size_t)ii * n + v, nv);
-        md::neg<L>(nv, nv);
+      double nv[C][L];
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        md::zero<L>(nv[c]);
+        if (row && col(c) && D > 1) {
+          ld<L>(NP, nn, (size_t)ii * n + lane + 64 * c, nv[c]);
+          md::neg<L>(nv[c], nv[c]);
+        }
       }
       __syncthreads();  // pre_0 is in slot 0
       for (int k = 0; k < D; ++k) {
-        double acc[L], r[L], x1[L];
+        double acc[L], r[L], x1[C][L];
         const double *slot = (k & 1) ? slot1 : slot0;
 #pragma unroll
         for (int l = 0; l < L; ++l) acc[l] = slot[l * 64 + lane];
         if (k >= 1) {
-          md::zero<L>(x1);
+#pragma unroll
+          for (int c = 0; c < C; ++c) md::zero<L>(x1[c]);
           const bool ok = row ? poll_dx(k - 1, x1) : true;
           if (!ok && lane == 0) sh_dead[k & 1] = 1;
 #pragma unroll
-          for (int l = 0; l < L; ++l) x1s[w][l * 64 + lane] = x1[l];
+          for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int l = 0; l < L; ++l) x1s[w][(c * L + l) * 64 + lane] = x1[c][l];
           __hip_atomic_store(&sh_x1[w], k, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-          MD<L>::fma_lazy(acc, nv, x1);
+#pragma unroll
+          for (int c = 0; c < C; ++c) MD<L>::fma_lazy(acc, nv[c], x1[c]);
         }
         if (row) {
           team_sum_lazy<L>(acc, 64);
@@ -1165,21 +1179,25 @@ __global__ void __launch_bounds__(256) stages_persistent_kernel(int n, int D, in
       return;
     }
     // companion wavefront
-    double m[L], pv[L], qv[L], x2[L], pre[L];
-    md::zero<L>(m);
-    md::zero<L>(pv);
-    md::zero<L>(qv);
-    md::zero<L>(x2);
+    double m[C][L], pv[C][L], qv[C][L], x2[C][L], pre[L];
     md::zero<L>(pre);
-    if (row && col) {
-      ld<L>(M, nn, (size_t)ii * n + v, m);
-      if (D > 2) ld<L>(NP + (size_t)L * nn, nn, (size_t)ii * n + v, pv);
-      if (D > 3) ld<L>(NP + (size_t)2 * L * nn, nn, (size_t)ii * n + v, qv);
-      md::neg<L>(pv, pv);
-      md::neg<L>(qv, qv);
-      double a[L];
-      ld_agent<L>(rT, nD, (size_t)v, a);
-      MD<L>::fma_lazy(pre, m, a);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      md::zero<L>(m[c]);
+      md::zero<L>(pv[c]);
+      md::zero<L>(qv[c]);
+      md::zero<L>(x2[c]);
+      if (row && col(c)) {
+        const size_t e = (size_t)ii * n + lane + 64 * c;
+        ld<L>(M, nn, e, m[c]);
+        if (D > 2) ld<L>(NP + (size_t)L * nn, nn, e, pv[c]);
+        if (D > 3) ld<L>(NP + (size_t)2 * L * nn, nn, e, qv[c]);
+        md::neg<L>(pv[c], pv[c]);
+        md::neg<L>(qv[c], qv[c]);
+        double a[L];
+        ld_agent<L>(rT, nD, (size_t)lane + 64 * c, a);
+        MD<L>::fma_lazy(pre, m[c], a);
+      }
     }
 #pragma unroll
     for (int l = 0; l < L; ++l) slot0[l * 64 + lane] = pre[l];
@@ -1201,12 +1219,14 @@ __global__ void __launch_bounds__(256) stages_persistent_kernel(int n, int D, in
           }
         }
         md::zero<L>(pre);
-        if (ok && col) {
-          double a[L];
-          ld_agent<L>(rT, nD, (size_t)(k + 1) * n + v, a);
-          MD<L>::fma_lazy(pre, m, a);
-          if (k >= 2) MD<L>::fma_lazy(pre, qv, x2);
-        }
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+          if (ok && col(c)) {
+            double a[L];
+            ld_agent<L>(rT, nD, (size_t)(k + 1) * n + lane + 64 * c, a);
+            MD<L>::fma_lazy(pre, m[c], a);
+            if (k >= 2) MD<L>::fma_lazy(pre, qv[c], x2[c]);
+          }
         if (k >= 1) {  // dx_{k-1} from the critical wavefront of this row
           long spins = 0;
           while (__hip_atomic_load(&sh_x1[w], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < k) {
@@ -1217,11 +1237,14 @@ __global__ void __launch_bounds__(256) stages_persistent_kernel(int n, int D, in
               break;
             }
           }
-          double x1[L];
 #pragma unroll
-          for (int l = 0; l < L; ++l) x1[l] = x1s[w][l * 64 + lane];
-          if (ok && col) MD<L>::fma_lazy(pre, pv, x1);
-          md::copy<L>(x1, x2);
+          for (int c = 0; c < C; ++c) {
+            double x1[L];
+#pragma unroll
+            for (int l = 0; l < L; ++l) x1[l] = x1s[w][(c * L + l) * 64 + lane];
+            if (ok && col(c)) MD<L>::fma_lazy(pre, pv[c], x1);
+            md::copy<L>(x1, x2[c]);
+          }
         }
         if (!ok && lane == 0) sh_dead[k & 1] = 1;
         double *slot = ((k + 1) & 1) ? slot1 : slot0;
@@ -1238,7 +1261,7 @@ __global__ void __launch_bounds__(256) stages_persistent_kernel(int n, int D, in
   const int team = tid / 16, tl = tid & 15;
   const int i = b * 16 + team;
   const bool live = i < n;
-  const int m0 = STAGE_PRODUCTS + 1 + g, m1 = m0 + Gm;
+  const int m0 = STAGE_PRODUCTS + 1 + (pairs ? 2 * g : g), m1 = pairs ? m0 + 1 : D;
   const int qlast = (m1 < D ? m1 : m0) - STAGE_PRODUCTS - 1;
   double acc0[L], acc1[L];  // lane-wise level sums of sum_q A_{m-q}(i, v) dx_q(v)
   md::zero<L>(acc0);
@@ -1259,12 +1282,14 @@ __global__ void __launch_bounds__(256) stages_persistent_kernel(int n, int D, in
     __syncthreads();
     if (tid == 0) __hip_atomic_fetch_add(rounds(mm), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  // the row's four terms A_{m0-q}(i, tl + 16 j) of the coming round, loaded
-  // while the previous round waits (they do not depend on dx)
-  double an[4][L];
+  // the row's terms A_{m0-q}(i, tl + 16 j) of the coming round, loaded while
+  // the previous round waits (they do not depend on dx); four quad doubles a
+  // lane, the others in the round, so that three workgroups fit a CU
+  constexpr int AHEAD = L == 4 ? 4 : 4 * C;
+  double an[AHEAD][L];
   auto fetch0 = [&](int q) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < AHEAD; ++j) {
       const int vv = tl + 16 * j;
       if (live && vv < n && q + STAGE_PRODUCTS + 1 <= m0)
         ld<L>(At + (size_t)(m0 - q) * nn, nnD, (size_t)i * n + vv, an[j]);
@@ -1291,19 +1316,25 @@ __global__ void __launch_bounds__(256) stages_persistent_kernel(int n, int D, in
           break;
         }
       }
-      xq[l * 64 + vv] = val;
+      xq[l * 64 * C + vv] = val;
     }
     if (__syncthreads_or(bad)) return;
     const bool use0 = q + STAGE_PRODUCTS + 1 <= m0, use1 = m1 < D && q + STAGE_PRODUCTS + 1 <= m1;
     if (live && use0) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < 4 * C; ++j) {
         const int vv = tl + 16 * j;
         if (vv < n) {
           double x[L];
 #pragma unroll
-          for (int l = 0; l < L; ++l) x[l] = xq[l * 64 + vv];
-          MD<L>::fma_lazy(acc0, an[j], x);
+          for (int l = 0; l < L; ++l) x[l] = xq[l * 64 * C + vv];
+          if (j < AHEAD) {
+            MD<L>::fma_lazy(acc0, an[j < AHEAD ? j : 0], x);
+          } else {
+            double a[L];
+            ld<L>(At + (size_t)(m0 - q) * nn, nnD, (size_t)i * n + vv, a);
+            MD<L>::fma_lazy(acc0, a, x);
+          }
         }
       }
     }
@@ -1312,7 +1343,7 @@ __global__ void __launch_bounds__(256) stages_persistent_kernel(int n, int D, in
       for (int vv = tl; vv < n; vv += 16) {
         double a[L], x[L];
 #pragma unroll
-        for (int l = 0; l < L; ++l) x[l] = xq[l * 64 + vv];
+        for (int l = 0; l < L; ++l) x[l] = xq[l * 64 * C + vv];
         ld<L>(At + (size_t)(m1 - q) * nn, nnD, (size_t)i * n + vv, a);
         MD<L>::fma_lazy(acc1, a, x);
       }
@@ -1725,7 +1756,34 @@ hipError_t launch_gemm(int L, int n, const double *M, const double *B, size_t b_
   return hipGetLastError();
 }
 
-bool stages_persistent(int L, int n, int D) { return (L == 2 || L == 4) && n <= 64 && D >= 1; }
+// Workgroups of the persistent staged solve: the solvers, and one updater per
+// 16 rows of a coefficient (from STAGE_PRODUCTS + 1 on), or of two
+// coefficients where one each would be more than 600 in all: the chip holds 768
+// (three a CU, 96 a chiplet), room for the solvers of another solve on every
+// chiplet beside all workgroups of this one, so that two solves at once cannot
+// hold each other up.  More than two coefficients an updater would slow the
+// chain: those sizes take one launch per stage.
+struct StagesGrid {
+  int solvers = 0, row_blocks = 0, groups = 0;
+  bool pairs = false, fits = false;
+};
+static StagesGrid stages_grid(int n, int D) {
+  StagesGrid g;
+  g.solvers = (n + 1) / 2;
+  g.row_blocks = (n + 15) / 16;
+  const int coeffs = D > STAGE_PRODUCTS + 1 ? D - STAGE_PRODUCTS - 1 : 0;
+  const int most = std::max(1, (600 - g.solvers) / g.row_blocks);
+  g.pairs = coeffs > most;
+  g.groups = g.pairs ? (coeffs + 1) / 2 : coeffs;
+  g.fits = g.groups <= most;
+  return g;
+}
+
+// Columns of the persistent solve: up to three a lane in double doubles, two
+// in quad doubles (registers).
+bool stages_persistent(int L, int n, int D) {
+  return ((L == 2 && n <= 192) || (L == 4 && n <= 128)) && D >= 1 && stages_grid(n, D).fits;
+}
 
 int stages_sync_ints(int D) { return (D + 2 + 64) * SYNC_STRIDE; }
 
@@ -1748,22 +1806,21 @@ hipError_t launch_stages_sync(int L, int n, int D, int *sync, double *dxT, hipSt
 hipError_t launch_stages(int L, int n, int D, const double *M, const double *NP, const double *At, double *rT,
                          double *dxT, int *sync, int32_t *status, hipStream_t st, bool sync_ready) {
   if (stages_persistent(L, n, D)) {
-    const int Gs = (n + 1) / 2, Bm = (n + 15) / 16;
-    // coefficient groups of the updaters: coefficients STAGE_PRODUCTS + 1 .. D - 1,
-    // one per group up to 64 of them, else two
-    const int C = D > STAGE_PRODUCTS + 1 ? D - STAGE_PRODUCTS - 1 : 0;
-    const int Gm = C <= 64 ? C : (C + 1) / 2;
-    const int G = Gs + Gm * Bm;  // at most 32 + 256 workgroups of 256 threads
+    const StagesGrid g = stages_grid(n, D);
+    const int G = g.solvers + g.groups * g.row_blocks;
     if (!sync_ready) {
       const hipError_t e = launch_stages_sync(L, n, D, sync, dxT, st);
       if (e != hipSuccess) return e;
     }
-    if (L == 2)
-      hipLaunchKernelGGL(stages_persistent_kernel<2>, dim3(G), dim3(256), 0, st, n, D, Gs, Gm, M, NP, At, rT, dxT,
-                         sync, status);
-    else
-      hipLaunchKernelGGL(stages_persistent_kernel<4>, dim3(G), dim3(256), 0, st, n, D, Gs, Gm, M, NP, At, rT, dxT,
-                         sync, status);
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(G), dim3(256), 0, st, n, D, g.solvers, g.pairs ? 1 : 0, M, NP, At, rT, dxT, sync,
+                         status);
+    };
+    if (L == 2 && n <= 64) run(stages_persistent_kernel<2, 1>);
+    else if (L == 2 && n <= 128) run(stages_persistent_kernel<2, 2>);
+    else if (L == 2) run(stages_persistent_kernel<2, 3>);
+    else if (n <= 64) run(stages_persistent_kernel<4, 1>);
+    else run(stages_persistent_kernel<4, 2>);
     return hipGetLastError();
   }
   const int crit_blocks = (n + 3) / 4;
