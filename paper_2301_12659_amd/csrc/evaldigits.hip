@@ -4,8 +4,8 @@
 // digits instead of multiple-double level sums.
 //
 // Work decomposition.  One workgroup per monomial, two teams of TL = 2 G2 lanes
-// (G2 = pair_lanes: 16, 32, 64 for orders up to 32, 64, 128).  Team A forms the
-// common factor, then team B the backward chain; then at every forward
+// (G2 = pair_lanes: 16, 32, 64 for orders up to 32, 64, 128).  They share the
+// products of the common factor and of the backward chain; then at every forward
 // step A forms f_j = f_{j-1} x_{v_j} while B forms the cross product
 // f_{j-1} b_{k-j} of the same f_{j-1} (values only: team A alone).  Within a
 // product the outputs are paired, o1 = p and o2 = D-1-p, so that every pair has
@@ -28,7 +28,9 @@
 // dependent instructions for the level sums.  The next term's digits are
 // loaded into the registers that the current term's rows leave.  Three series
 // instead of four (the common factor beside the backward chain) leave room for
-// two workgroups per CU at order 128 in octo doubles.
+// two workgroups per CU at order 128 in octo doubles.  Measured (octo double, 128
+// variables, 512 monomials, order 128; evaldiff.hip 43.9 ms): 17.9 ms with
+// the single products formed by one team while the other waits, 13.7 shared.
 #include "digits.hpp"
 #include "evaldiff_dev.hpp"
 
@@ -100,13 +102,13 @@ __device__ __forceinline__ void chunk_exponents(const DigitSeries &U, const Digi
   for (int e = 0; e < 4; ++e) sum[e] = u[e] + v[t.o < 0 ? 0 : -e];
 }
 
-// The largest exponents R1, R2 of the terms of outputs o1 and o2 in the lane's
-// half.
+// The largest exponents R1, R2 of the terms of outputs o1 and o2 in chunks
+// cbeg .. cend - 1 of the lane's half.
 __device__ __forceinline__ void digit_exponents(const DigitSeries &U, const DigitSeries &V, const DigitLane &q, int &R1,
-                                                int &R2) {
+                                                int &R2, int cbeg, int cend) {
   R1 = R2 = 2 * DIGIT_ZERO;
 #pragma unroll 2
-  for (int c = 0; c < q.chunks; ++c) {
+  for (int c = cbeg; c < cend; ++c) {
     const DigitChunk t = digit_chunk(q, c);
     int s[4];
     chunk_exponents(U, V, t, s);
@@ -121,11 +123,12 @@ __device__ __forceinline__ void digit_exponents(const DigitSeries &U, const Digi
 // it.  Half 0 has only terms of o2, with the same i in all lanes (U is read as
 // a broadcast), and so does half 1 until its lanes turn to o1 one after the
 // other.  Half 0 finishes o2 and half 1 o1; half 1's part of o2 is parked in
-// other, as digits.  Returns false where a term needed more than DIGIT_PAD
-// rows of shift (WIDE: never).
+// other, as digits.  Chunks cbeg .. cend - 1 of the half: the others are another
+// team's, whose z and other add to these.  Returns false where a term needed
+// more than DIGIT_PAD rows of shift (WIDE: never).
 template <int S, int Dp, bool WIDE>
 __device__ __forceinline__ bool conv_digits(const DigitSeries &U, const DigitSeries &V, const DigitLane &q, int R1,
-                                            int R2, double (&z)[S], double (&other)[S]) {
+                                            int R2, int cbeg, int cend, double (&z)[S], double (&other)[S]) {
   bool far = false;
   const double *up, *vp;
   int vrow = 0;  // WIDE: -delta
@@ -159,7 +162,7 @@ __device__ __forceinline__ bool conv_digits(const DigitSeries &U, const DigitSer
   double acc[S], u[S], v[S];
 #pragma unroll
   for (int k = 0; k < S; ++k) acc[k] = other[k] = 0.0;
-  fetch(0);
+  fetch(cbeg);
   locate(tn, dn[0], 0);
 #pragma unroll
   for (int k = 0; k < S; ++k) {
@@ -169,7 +172,7 @@ __device__ __forceinline__ bool conv_digits(const DigitSeries &U, const DigitSer
   constexpr int FLUSH = 504 / S / 4;  // chunks between carries: sums of at most 504 products
   int since = 0;
 #pragma unroll 1
-  for (int c = 0; c < q.chunks; ++c) {
+  for (int c = cbeg; c < cend; ++c) {
     if (q.c0 + c == q.nc2 && q.half) {  // o2 complete
 #pragma unroll
       for (int k = 0; k < S; ++k) {
@@ -180,7 +183,7 @@ __device__ __forceinline__ bool conv_digits(const DigitSeries &U, const DigitSer
     t = tn;
 #pragma unroll
     for (int e = 0; e < 4; ++e) d[e] = dn[e];
-    fetch(c + 1);  // past the last chunk: another half's or masked, unused
+    fetch(c + 1);  // past the last chunk: another part's or masked, unused
 #pragma unroll(S <= 12 && !WIDE ? 4 : 1)
     for (int e = 0; e < 4; ++e) {
       // the next term's digits arrive while this one's rows run
@@ -208,7 +211,7 @@ __device__ __forceinline__ bool conv_digits(const DigitSeries &U, const DigitSer
       carry_digits<S>(acc);
     }
   }
-  if (q.c0 + q.chunks == q.nc2 && q.half) {  // a lane whose o1 is o2
+  if (q.c0 + cend <= q.nc2 && q.half) {  // all of it o2
 #pragma unroll
     for (int k = 0; k < S; ++k) {
       other[k] = acc[k];
@@ -242,15 +245,16 @@ __device__ void eval_monomial_digits(const EvalArgs &a, int mono, char *lds) {
   const DigitLane q = digit_lane<G2>(Dc, tl);
   const bool owner = q.own >= 0;
   const int s = owner ? q.own : 0;
-  // LDS: U [S][Dp], per team V [PAD + S][Dp], the exponents of each, per team
-  // the halves' exchange of exponents (order above 64)
+  // LDS: U [S][Dp], per team V [PAD + S][Dp], the exponents of each, the
+  // exchange of the largest exponents
   const size_t ud = (size_t)S * Dp, vd = (size_t)(S + DIGIT_PAD) * Dp;
   double *base = reinterpret_cast<double *>(lds);
   const int teams = derivs ? 2 : 1, team = isA ? 0 : 1;
   int *rbase = reinterpret_cast<int *>(base + ud + teams * vd);
   const DigitSeries U{base, rbase + 4};
   const DigitSeries V{base + ud + team * vd + (size_t)DIGIT_PAD * Dp, rbase + (1 + team) * RP + 4};
-  int *rx = rbase + (1 + teams) * RP + team * 2 * TL;
+  const DigitSeries VA{base + ud + (size_t)DIGIT_PAD * Dp, rbase + RP + 4};
+  int *rx = rbase + (1 + teams) * RP;  // [team][2 TL]
   for (int k = tl; k < DIGIT_PAD * Dp; k += TL) V.d[k - DIGIT_PAD * Dp] = 0.0;
   for (int k = tid; k < (1 + teams) * RP; k += blockDim.x) rbase[k] = DIGIT_MASK;
   if (isA && tl < S) U.d[tl * Dp + Dc] = 0.0;
@@ -294,9 +298,11 @@ __device__ void eval_monomial_digits(const EvalArgs &a, int mono, char *lds) {
   int nbig = 0;
   for (int j = 0; j < k; ++j) nbig += a.exp[e0 + j] >= 2 ? 1 : 0;
   const bool f0_scalar = nbig == 0;
-  // steps with a product: team A's common factor CF = prod x^(a-1), team B's
-  // backward chain b_q, q = 2..k-1, parked in the slot of entry k-q-1, then
-  // the forward chain (A) beside the cross products (B)
+  // steps with a product: the common factor CF = prod x^(a-1), the backward
+  // chain b_q, q = 2..k-1, parked in the slot of entry k-q-1, then the forward
+  // chain (A) beside the cross products (B).  Where there is one product only
+  // (before the forward chain, and its last step) the teams share it: each
+  // takes half of the chunks, A finishes.
   const int steps_a = max(nbig - 1, 0), steps_b = derivs ? max(k - 2, 0) : 0;
   double f[L], r[L];
   md::zero<L>(f);
@@ -309,14 +315,14 @@ __device__ void eval_monomial_digits(const EvalArgs &a, int mono, char *lds) {
     if (p == 1) load(a.x, xls, (size_t)v * D, w);
     else load(a.pw + (size_t)(p - 2) * L * nD, nD, (size_t)v * D, w);
   };
-  if (isA && !f0_scalar) load_cf(f);
-  if (!isA && steps_b > 0) load_x(k - 1, r);  // b_1
+  if (!f0_scalar) load_cf(f);
   const bool track = a.vsize != nullptr;
   double vmax = 0.0;
   const int start = steps_a + steps_b, total = start + k;
   for (int t = 0; t < total; ++t) {
     const int j = t - start + 1;  // forward step (from 1), else an earlier one
     const int ej = j - 1, aj = j >= 1 ? a.exp[e0 + ej] : 1;
+    if (j == 1 && steps_b > 0) sync();  // team B reads the parked products, which A stored
     if (j == 1 && isA) {  // f_0 = c CF (c in coefficient 0 without a common factor)
       if (!f0_scalar) {
         double w[L];
@@ -329,57 +335,74 @@ __device__ void eval_monomial_digits(const EvalArgs &a, int mono, char *lds) {
       vmax = fabs(f[0]);
     }
     const bool first = t < steps_a, back = !first && j < 1, scalar = f0_scalar && j == 1;
-    const bool run = first ? isA : back ? !isA : (isA || j < k);
-    if (run) {
-      double w[L];  // the operand V
+    const bool single = first || back || j == k;  // one product only
+    const bool joint = single && teams == 2 && !scalar;
+    const bool takes_v = joint ? !isA : (isA || !single);  // loads the operand V
+    if (takes_v) {
+      double w[L];
       if (first) load_cf(w);
       else if (back) load_x(k - 2 - (t - steps_a), w);  // x_{v_{k-q+1}}, q - 2 = t - steps_a
-      else if (isA) load_x(ej, w);
+      else if (isA || j == k) load_x(ej, w);
       else if (k - j == 1) load_x(k - 1, w);  // b_1 = x_{v_k}
       else load(a.der, zD, (size_t)(e0 + ej) * D, w);  // b_{k-j}
-      if (derivs && j == k) {  // (team A) d/dx_{v_k} = a_k f_{k-1}
-        md::copy<L>(f, r);
-        md::mul_int<L>(r, aj);
-        store_der(ej, r);
-      }
       if (scalar) {  // times the coefficient
+        if (derivs && j == k) {  // (team A) d/dx_{v_k} = a_k f_{k-1}
+          md::copy<L>(f, r);
+          md::mul_int<L>(r, aj);
+          store_der(ej, r);
+        }
         MD<L>::mul(c, w, r);
       } else {
-        if (isA || back) {
-          if (isA) md::copy<L>(f, r);
-          put(U, r);
-        }
-        put(V, w);
+        put(joint ? VA : V, w);
       }
+    } else if (first) {
+      int skip = next;  // (both teams count the factors)
+      while (a.exp[e0 + skip] < 2) ++skip;
+      next = skip + 1;
     }
     if (!scalar) {  // r = U V, this lane's coefficient; U and V are free afterwards
+      if (isA) {
+        if (derivs && j == k) {  // d/dx_{v_k} = a_k f_{k-1}
+          md::copy<L>(f, r);
+          md::mul_int<L>(r, aj);
+          store_der(ej, r);
+        }
+        if (!back) md::copy<L>(f, r);
+        else if (t == steps_a) load_x(k - 1, r);  // b_1
+        put(U, r);
+      }
       sync();
+      const bool run = joint || takes_v;
+      const DigitSeries W = joint ? VA : V;
+      const int part = (q.chunks + 1) / 2;
+      const int cbeg = joint && !isA ? part : 0, cend = joint && isA ? part : q.chunks;
       double z[S], other[S];
       int R1 = 0, R2 = 0;
-      if (run) digit_exponents(U, V, q, R1, R2);
-      if (G2 < 64) {
+      if (run) digit_exponents(U, W, q, R1, R2, cbeg, cend);
+      if (G2 < 64 && !joint) {
         R1 = max(R1, __shfl_xor(R1, G2, 64));
         R2 = max(R2, __shfl_xor(R2, G2, 64));
       } else {
-        if (run) {
-          rx[2 * tl] = R1;
-          rx[2 * tl + 1] = R2;
-        }
+        rx[(team * TL + tl) * 2] = R1;
+        rx[(team * TL + tl) * 2 + 1] = R2;
         sync();
-        if (run) {
-          R1 = max(R1, rx[2 * (tl ^ G2)]);
-          R2 = max(R2, rx[2 * (tl ^ G2) + 1]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int other_team = joint ? (e >> 1) : team;
+          const int o = other_team * TL + ((e & 1) ? tl ^ G2 : tl);
+          R1 = max(R1, rx[2 * o]);
+          R2 = max(R2, rx[2 * o + 1]);
         }
       }
       if (run) {
-        if (!__all(conv_digits<S, Dp, false>(U, V, q, R1, R2, z, other)))
-          conv_digits<S, Dp, true>(U, V, q, R1, R2, z, other);
+        if (!__all(conv_digits<S, Dp, false>(U, W, q, R1, R2, cbeg, cend, z, other)))
+          conv_digits<S, Dp, true>(U, W, q, R1, R2, cbeg, cend, z, other);
       } else {
 #pragma unroll
         for (int p = 0; p < S; ++p) z[p] = other[p] = 0.0;
       }
-      // half 1's part of o2 to the lane of half 0
-      if (G2 < 64) {
+      // half 1's part of o2 to the lane of half 0, team B's share to team A
+      if (G2 < 64 && !joint) {
 #pragma unroll
         for (int p = 0; p < S; ++p) {
           const double o = __shfl_xor(other[p], G2, 64);
@@ -388,27 +411,47 @@ __device__ void eval_monomial_digits(const EvalArgs &a, int mono, char *lds) {
         sync();
       } else {  // through V
         sync();
-        if (run && q.half)
+        const bool send = joint && !isA;
+        if (run && q.half) {
 #pragma unroll
-          for (int p = 0; p < S; ++p) V.d[p * Dp + q.p] = other[p];
+          for (int p = 0; p < S; ++p) W.d[p * Dp + q.p + (send ? G2 : 0)] = other[p];
+        }
+        if (joint) {
+          carry_digits<S>(z);
+          if (send) {
+#pragma unroll
+            for (int p = 0; p < S; ++p) V.d[p * Dp + tl] = z[p];
+          }
+        }
         sync();
-        if (run && !q.half)
+        if (run && !send) {
+          if (!q.half) {
 #pragma unroll
-          for (int p = 0; p < S; ++p) z[p] += V.d[p * Dp + q.p];
+            for (int p = 0; p < S; ++p) z[p] += W.d[p * Dp + q.p];
+          }
+          if (joint) {
+            const double *zb = base + ud + vd + (size_t)DIGIT_PAD * Dp;
+#pragma unroll
+            for (int p = 0; p < S; ++p) {
+              if (!q.half) z[p] += W.d[p * Dp + q.p + G2];
+              z[p] += zb[p * Dp + tl];
+            }
+          }
+        }
         sync();
       }
-      if (run) from_digits<L, S>(z, q.half ? R1 : R2, r);
+      if (run && !(joint && !isA)) from_digits<L, S>(z, q.half ? R1 : R2, r);
     }
-    if (run) {
-      if (isA) {
-        md::copy<L>(r, f);
-        if (j >= 1) vmax = fmax(vmax, fabs(f[0]));
-      } else if (back) {
+    if (isA) {
+      if (back) {
         store_der(k - 3 - (t - steps_a), r);
       } else {
-        md::mul_int<L>(r, aj);
-        store_der(ej, r);
+        md::copy<L>(r, f);
+        if (j >= 1) vmax = fmax(vmax, fabs(f[0]));
       }
+    } else if (!single) {
+      md::mul_int<L>(r, aj);
+      store_der(ej, r);
     }
   }
   if (isA && owner) {
@@ -423,7 +466,10 @@ __global__ void __launch_bounds__(4 * G2, 2) evaldiff_digits_kernel(EvalArgs a) 
   eval_monomial_digits<L, G2>(a, __builtin_amdgcn_readfirstlane(a.order[blockIdx.x]), ldsc);
 }
 
-// Orders whose products fill a team of at least 32 lanes.
+// Orders whose products fill a team of at least 32 lanes; measured in octo
+// doubles at order 47: 537 us by level sums, 279 on digits.  Quad doubles stay with the
+// level sums: 112 instructions per term against 78, and the digits' alignment
+// and rounding cost more than that saves (order 64: 243 us against 316).
 bool evaldiff_on_digits(int L, int Dc) { return L == 8 && Dc > 16; }
 
 template <int L, int G2>
