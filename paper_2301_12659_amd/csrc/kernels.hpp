@@ -69,8 +69,7 @@ hipError_t launch_assemble(int L, int n, int D, int Dc, int m, int nnz, const in
                            const double *vsize = nullptr, TOut rt = TOut(), TOut at = TOut(), int *clear = nullptr,
                            int clear_count = 0, double *empty = nullptr, size_t empty_count = 0,
                            CountWait wait = CountWait());
-size_t evaldiff_lds_bytes(int L, int D);
-int evaldiff_workers_per_block(int D);  // monomials per 256-thread workgroup
+int evaldiff_workers_per_block(int D);  // monomials per workgroup (two teams of lanes each)
 hipError_t launch_assemble_b(int L, int n, int D, int Dc, int m, const int32_t *poly_ptr, const double *cst,
                              const double *val, double *b, hipStream_t st, double *tsz = nullptr,
                              const double *vsize = nullptr, TOut rt = TOut(), int *clear = nullptr,
