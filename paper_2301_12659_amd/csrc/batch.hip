@@ -1,20 +1,29 @@
 // Newton steps for a batch of independent polynomial systems ("paths") of
-// uneven size in one persistent launch.  The paper tracks many solution
-// paths of a homotopy (Section 1); each path is one system p(x; c) = 0 with
-// its own n, truncation degree d and monomials, and one step of every path
-// is the Newton step of Section 2.
+// uneven size.  The paper tracks many solution paths of a homotopy (Section 1);
+// each path is one system p(x; c) = 0 with its own n, truncation degree d and
+// monomials, and one step of every path is the Newton step of Section 2.
 //
-// Work decomposition.  A grid of G workgroups (G <= 2 per CU) takes paths
-// from a queue, most expensive first, and runs the whole step of a path
-// itself: the evaluation and differentiation by convolutions (the workers
-// of evaldiff_dev.hpp), the assembly of b(t) and of the Jacobian series
-// (coefficient-major, A_k contiguous), the Householder QR of A_0 with Q^T,
-// M = R^{-1} Q^T, N = M A_1, the stages dx_k = M r_k - N dx_{k-1} with the
-// later right-hand sides pushed r_m -= A_{m-k} dx_k, and x := x + dx.  Each
-// workgroup has its own slot of device memory for the intermediates of one
-// path, so the workspace is G slots, not one per path.  The phases of a path
-// are separated by workgroup barriers only; no workgroup waits for another,
-// and every workgroup leaves when the queue is empty.
+// Work decomposition.  Every phase of a step is one launch over all paths of a
+// chunk: a path's work is spread over the chip, and the paths' tails overlap.
+//   evaluation and differentiation, one launch per width of a monomial's
+//     teams of lanes (evaldiff_dev.hpp), the monomials longest first;
+//   assembly of b(t) and of the Jacobian series (coefficient-major, A_k
+//     contiguous);
+//   M = A_0^{-1} by refinement from an inverse in doubles, one workgroup per
+//     path and then per row (inverse_dev.hpp); the Householder QR of A_0 with
+//     Q^T and M = R^{-1} Q^T for the paths it does not suit;
+//   N = M A_1;
+//   the stages dx_k = M r_k - N dx_{k-1}, r_m -= A_{m-k} dx_k in blocks of
+//     four: the stages of a block by one workgroup per path, the later
+//     right-hand sides by the whole grid;
+//   x := x + dx, norms and status.
+// The workspace is G (2 per CU) times the largest path's intermediates; paths
+// that do not fit it together are run in chunks.
+// Measured (quad double, 1024 paths of n = 16..96, 16, 32 or 64 coefficients, 8
+// to 32 monomials per polynomial): 126 ms with the whole step of a path in one
+// workgroup, where the largest path, on its own at the end, was the bound;
+// 68 ms in phases: evaluation 29, updates 16, refinement 11, stages 5, assembly
+// 4.5, N 2.2.
 //
 // Mixed precision (Section 1): the residual and the update at L limbs, the
 // Jacobian, the QR and the stages at Ls <= L limbs (the leading limb planes
@@ -32,6 +41,7 @@
 #include <vector>
 
 #include "evaldiff_dev.hpp"
+#include "inverse_dev.hpp"
 
 namespace mdk {
 
@@ -43,9 +53,9 @@ struct PathMeta {
 };
 
 struct BatchArgs {
-  int P;                                   // paths to run (entries of order)
   const PathMeta *meta;
   const int32_t *order;
+  const long long *off;                    // per entry of order: its path's bytes in slots
   const int32_t *poly_ptr, *mon_ptr, *var, *exp, *asm_ptr, *asm_ent;
   const int32_t *tile;                     // team lanes per bucket
   const double *cff, *cst;
@@ -54,9 +64,75 @@ struct BatchArgs {
   int32_t *status;                         // per path
   double *norms;                           // per path: max |b|, max |dx|
   char *slots;
-  size_t slot_bytes;
-  int *queue;
 };
+
+// The intermediates of one path.
+template <int L, int Ls> struct PathSlot {
+  double *val, *der, *b, *At, *qr, *qt, *tau, *invd, *M, *N, *r, *dx;
+};
+template <int L, int Ls>
+__device__ __forceinline__ PathSlot<L, Ls> path_slot(const PathMeta &pm, double *slot) {
+  const size_t n = pm.n, D = pm.D, nn = n * n, nD = n * D, nnD = nn * D;
+  auto take = [&](size_t cnt) {
+    double *q = slot;
+    slot += (cnt + 31) & ~(size_t)31;
+    return q;
+  };
+  PathSlot<L, Ls> w;
+  w.val = take((size_t)L * pm.m * D);
+  w.der = take((size_t)L * pm.nnz * D);
+  w.b = take((size_t)L * nD);
+  w.At = take((size_t)Ls * nnD);
+  w.qr = take((size_t)Ls * nn);
+  w.qt = take((size_t)Ls * nn);
+  w.tau = take((size_t)Ls * n);
+  w.invd = take((size_t)Ls * n);
+  w.M = take((size_t)Ls * nn);
+  w.N = take((size_t)Ls * nn);
+  w.r = take((size_t)Ls * nD);
+  w.dx = take((size_t)Ls * nD);
+  return w;
+}
+
+// 1. Evaluation and differentiation of the monomials work[0 .. count) =
+// (entry of order, monomial) of the paths whose order has G2 = pair_lanes,
+// teams of lanes as in evaldiff.hip.  LIMBS = L: the values, with the
+// derivatives when Ls == L; LIMBS = Ls < L: the derivatives alone.
+template <int L, int Ls, int LIMBS, int G2>
+__global__ void __launch_bounds__((8 * G2 > 64 ? 8 * G2 : 64), 4) batch_eval_kernel(BatchArgs B, const int2 *work,
+                                                                                    int count) {
+  extern __shared__ __align__(16) double lds[];
+  constexpr bool VALUES = LIMBS == L, DERIVS = LIMBS == Ls;
+  constexpr int lanes = (DERIVS ? 8 : 4) * G2, per = 8 * G2 < 64 ? 64 / lanes : 1;
+  const int w = per == 1 ? 0 : threadIdx.x / lanes, idx = blockIdx.x * per + w;
+  if (idx >= count) return;
+  int pos = work[idx].x, mono = work[idx].y;
+  if constexpr (per == 1) {
+    pos = __builtin_amdgcn_readfirstlane(pos);
+    mono = __builtin_amdgcn_readfirstlane(mono);
+  }
+  const PathMeta pm = B.meta[B.order[pos]];
+  const PathSlot<L, Ls> s = path_slot<L, Ls>(pm, reinterpret_cast<double *>(B.slots + B.off[pos]));
+  EvalArgs a;
+  a.n = pm.n;
+  a.D = pm.D;
+  a.Dc = pm.D;
+  a.m = pm.m;
+  a.nnz = pm.nnz;
+  a.mon_ptr = B.mon_ptr + pm.mon_off;
+  a.var = B.var + pm.ent_off;
+  a.exp = B.exp + pm.ent_off;
+  a.order = nullptr;  // not read: monomials are addressed directly
+  a.cff = B.cff + pm.cff_off;
+  a.x = B.x + pm.x_off;
+  a.pw = a.x;  // not read: batched paths have exponents of at most 2, no power table
+  a.val = VALUES ? s.val : nullptr;
+  a.der = s.der;
+  a.x_ls = B.x_ls;
+  a.cff_ls = B.cff_ls;
+  a.values_only = DERIVS ? 0 : 1;
+  eval_monomial_team<LIMBS, G2>(a, mono, threadIdx.x - w * lanes, lds + (size_t)w * team_doubles<LIMBS, G2>());
+}
 
 constexpr int BATCH_NT = 256;
 constexpr int BATCH_MAXN = 128;  // rows per lane <= 2 in the back substitution
@@ -102,103 +178,134 @@ __device__ double block_max(double v, double *sh) {
   return r;
 }
 
+// Blocks of a launch over paths: blockIdx.x is the entry of order, blockIdx.y
+// and gridDim.y split the path's work.
 template <int L, int Ls>
-__device__ void path_step(const BatchArgs &B, const PathMeta &pm, int p, double *slot, double *lds, double *shr,
-                          int &sh_sing) {
+__device__ __forceinline__ PathSlot<L, Ls> block_path(const BatchArgs &B, PathMeta &pm) {
+  pm = B.meta[B.order[blockIdx.x]];
+  return path_slot<L, Ls>(pm, reinterpret_cast<double *>(B.slots + B.off[blockIdx.x]));
+}
+
+// 2. Assembly: b = -(c_0 + sum of the row's monomial values) at L limbs and
+// its coefficient-major leading limbs r[k][i]; the Jacobian series,
+// coefficient-major At[k][i][j], and A_0 once more for a factorization.  A
+// unit is a tile of `tile_rows` entries (i, j) with all their coefficients,
+// turned through LDS so that both sides move whole cache lines, or 256
+// entries of b.  Bound by HBM.
+__host__ __device__ inline int tile_rows(int D) { return D <= 64 ? 16 : 8; }
+
+template <int L, int Ls>
+__global__ void __launch_bounds__(BATCH_NT) batch_assemble_kernel(BatchArgs B) {
+  extern __shared__ double lds[];
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
   const int tid = threadIdx.x, NT = blockDim.x;
-  const int n = pm.n, D = pm.D, m = pm.m, nnz = pm.nnz;
-  const int T = B.tile[pm.bucket];
-  const int team = tid / T, tl = tid % T, nteams = NT / T;
+  const int n = pm.n, D = pm.D, m = pm.m, nnz = pm.nnz, R = tile_rows(D), Rp = R + 1;
   const size_t nn = (size_t)n * n, nD = (size_t)n * D, nnD = nn * D;
-  size_t off = 0;
-  auto take = [&](size_t cnt) {
-    double *q = slot + off;
-    off += (cnt + 31) & ~(size_t)31;
-    return q;
-  };
-  double *val = take((size_t)L * m * D), *der = take((size_t)L * nnz * D), *b = take((size_t)L * nD);
-  double *At = take((size_t)Ls * nnD), *qr = take((size_t)Ls * nn), *qt = take((size_t)Ls * nn);
-  double *tau = take((size_t)Ls * n), *invd = take((size_t)Ls * n), *M = take((size_t)Ls * nn);
-  double *N = take((size_t)Ls * nn), *r = take((size_t)Ls * nD), *dx = take((size_t)Ls * nD);
   const int32_t *poly_ptr = B.poly_ptr + pm.poly_off, *asm_ptr = B.asm_ptr + pm.asm_off;
   const int32_t *asm_ent = B.asm_ent + pm.asment_off;
   const double *cst = B.cst + pm.x_off;
-  double *x = B.x + pm.x_off;
-  if (tid == 0) sh_sing = 0;
-
-  // 1. evaluation: values at L limbs (with the derivatives when Ls == L)
-  EvalArgs a;
-  a.n = n;
-  a.D = D;
-  a.Dc = D;
-  a.m = m;
-  a.nnz = nnz;
-  a.mon_ptr = B.mon_ptr + pm.mon_off;
-  a.var = B.var + pm.ent_off;
-  a.exp = B.exp + pm.ent_off;
-  a.order = a.mon_ptr;  // not read: monomials are addressed directly
-  a.cff = B.cff + pm.cff_off;
-  a.x = x;
-  a.pw = x;  // not read: batched paths have exponents of at most 2, no power table
-  a.val = val;
-  a.der = der;
-  a.x_ls = B.x_ls;
-  a.cff_ls = B.cff_ls;
-  a.values_only = (Ls == L) ? 0 : 1;
-  {
-    const int Gw = worker_lanes(D), wpb = NT / Gw, wid = tid / Gw, wl = tid - wid * Gw;
-    double *wbuf = lds + (size_t)wid * 3 * L * (D + 1);
-    for (int mono = wid; mono < m; mono += wpb) eval_monomial<L>(a, mono, wl, wbuf);
-  }
-  __syncthreads();
-  // 2. b = -(c_0 + sum of the row's monomial values), L limbs
-  for (int q = tid; q < (int)nD; q += NT) {
-    const int i = q / D, s = q - i * D;
-    double acc[L];
-    ld<L>(cst, B.x_ls, (size_t)q, acc);
-    for (int mj = poly_ptr[i]; mj < poly_ptr[i + 1]; ++mj) {
-      double v[L], t[L];
-      ld<L>(val, (size_t)m * D, (size_t)mj * D + s, v);
-      MD<L>::add(acc, v, t);
-      md::copy<L>(t, acc);
-    }
-    md::neg<L>(acc, acc);
-    st<L>(b, nD, q, acc);
-  }
-  __syncthreads();
-  if (Ls != L) {  // the derivatives at Ls limbs
-    a.values_only = 0;
-    const int Gw = worker_lanes(D), wpb = NT / Gw, wid = tid / Gw, wl = tid - wid * Gw;
-    double *wbuf = lds + (size_t)wid * 3 * Ls * (D + 1);
-    for (int mono = wid; mono < m; mono += wpb) eval_monomial<Ls>(a, mono, wl, wbuf);
-    __syncthreads();
-  }
-  // 3. the Jacobian series, coefficient-major At[k][i][j]; A_0 into qr, I into qt
-  for (size_t q = tid; q < nnD; q += NT) {
-    const size_t ij = q / D;
-    const int s = (int)(q - ij * D);
-    double acc[Ls];
-    md::zero<Ls>(acc);
-    const int lo = asm_ptr[ij], hi = asm_ptr[ij + 1];
-    if (lo < hi) {
-      ld<Ls>(der, (size_t)nnz * D, (size_t)asm_ent[lo] * D + s, acc);
-      for (int t = lo + 1; t < hi; ++t) {
-        double v[Ls], w[Ls];
-        ld<Ls>(der, (size_t)nnz * D, (size_t)asm_ent[t] * D + s, v);
-        MD<Ls>::add(acc, v, w);
-        md::copy<Ls>(w, acc);
+  const int tiles = (int)((nn + R - 1) / R), units = tiles + (int)((nD + NT - 1) / NT);
+  for (int unit = blockIdx.y; unit < units; unit += gridDim.y) {
+    if (unit < tiles) {
+      const int ij0 = unit * R, rows = min(R, (int)nn - ij0);
+      for (int q = tid; q < rows * D; q += NT) {
+        const int row = q / D, s = q - row * D, ij = ij0 + row;
+        double acc[Ls];
+        md::zero<Ls>(acc);
+        const int lo = asm_ptr[ij], hi = asm_ptr[ij + 1];
+        if (lo < hi) {
+          ld<Ls>(w.der, (size_t)nnz * D, (size_t)asm_ent[lo] * D + s, acc);
+          for (int t = lo + 1; t < hi; ++t) {
+            double v[Ls], y[Ls];
+            ld<Ls>(w.der, (size_t)nnz * D, (size_t)asm_ent[t] * D + s, v);
+            MD<Ls>::add(acc, v, y);
+            md::copy<Ls>(y, acc);
+          }
+        }
+#pragma unroll
+        for (int l = 0; l < Ls; ++l) lds[(l * D + s) * Rp + row] = acc[l];
+        if (s == 0) st<Ls>(w.qr, nn, ij, acc);
+      }
+      __syncthreads();
+      for (int q = tid; q < R * D; q += NT) {
+        const int s = q / R, row = q - s * R;
+        if (row < rows)
+#pragma unroll
+          for (int l = 0; l < Ls; ++l) w.At[(size_t)l * nnD + (size_t)s * nn + ij0 + row] = lds[(l * D + s) * Rp + row];
+      }
+      __syncthreads();
+    } else {
+      const int q = (unit - tiles) * NT + tid;
+      if (q < (int)nD) {
+        const int i = q / D, s = q - i * D;
+        double acc[L];
+        ld<L>(cst, B.x_ls, (size_t)q, acc);
+        for (int mj = poly_ptr[i]; mj < poly_ptr[i + 1]; ++mj) {
+          double v[L], y[L];
+          ld<L>(w.val, (size_t)m * D, (size_t)mj * D + s, v);
+          MD<L>::add(acc, v, y);
+          md::copy<L>(y, acc);
+        }
+        md::neg<L>(acc, acc);
+        st<L>(w.b, nD, q, acc);
+#pragma unroll
+        for (int l = 0; l < Ls; ++l) w.r[(size_t)l * nD + (size_t)s * n + i] = acc[l];
       }
     }
-    st<Ls>(At, nnD, (size_t)s * nn + ij, acc);
-    if (s == 0) {
-      st<Ls>(qr, nn, ij, acc);
-      const int i = (int)(ij / n), j = (int)(ij - (size_t)i * n);
+  }
+}
+
+// 3. M = A_0^{-1} by refinement from an inverse in doubles (inverse.hip):
+// the inverse X goes into the space of Q^T, the word that asks for the
+// factorization into that of tau.
+template <int L, int Ls>
+__device__ __forceinline__ int *path_need(const PathSlot<L, Ls> &w) {
+  return reinterpret_cast<int *>(w.tau);
+}
+template <int L, int Ls, int RW, int NB, int NW>
+__global__ void __launch_bounds__(64 * NW) batch_inv64_kernel(BatchArgs B, int lo) {
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  if (pm.n <= lo || pm.n > NB * NW) return;
+  inv64_matrix<RW, NB, NW>(pm.n, w.qr, w.qt, path_need(w));
+}
+// (sizes lo < n <= hi; grid.y: rows)
+template <int L, int Ls>
+__global__ void __launch_bounds__(RefineThreads<Ls>::value) batch_refine_kernel(BatchArgs B, int lo, int hi, int S) {
+  extern __shared__ double lds[];
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  if (pm.n <= lo || pm.n > hi || (int)blockIdx.y >= pm.n) return;
+  refine_row<Ls>(pm.n, S, blockIdx.y, w.qr, w.qt, w.M, path_need(w), lds);
+}
+
+// The same by a factorization, for the paths whose A_0 asked for it; sing: A_0
+// is singular to working precision.
+template <int L, int Ls>
+__global__ void __launch_bounds__(BATCH_NT) batch_factor_kernel(BatchArgs B) {
+  __shared__ double shr[8 * 8 + 16];
+  __shared__ int sh_sing;
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  const int tid = threadIdx.x, NT = blockDim.x, n = pm.n;
+  int *flags = path_need(w);
+  const bool needed = flags[0] != 0;
+  __syncthreads();
+  if (tid == 0) flags[1] = 0;
+  if (!needed) return;
+  const int T = B.tile[pm.bucket];
+  const int team = tid / T, tl = tid % T, nteams = NT / T;
+  const size_t nn = (size_t)n * n;
+  double *qr = w.qr, *qt = w.qt, *invd = w.invd, *M = w.M;
+  if (tid == 0) sh_sing = 0;
+  for (int q = tid; q < (int)nn; q += NT) {
+    const int i = q / n, j = q - i * n;
 #pragma unroll
-      for (int l = 0; l < Ls; ++l) qt[(size_t)l * nn + ij] = (l == 0 && i == j) ? 1.0 : 0.0;
-    }
+    for (int l = 0; l < Ls; ++l) qt[(size_t)l * nn + q] = (l == 0 && i == j) ? 1.0 : 0.0;
   }
   __syncthreads();
-  // 4. Householder QR of A_0 (row-major, in place) with Q^T
+  // Householder QR of A_0 (row-major, in place) with Q^T
   for (int c = 0; c < n; ++c) {
     double u[Ls], nrm2[Ls];
     md::zero<Ls>(u);
@@ -232,7 +339,6 @@ __device__ void path_step(const BatchArgs &B, const PathMeta &pm, int p, double 
       for (int l = 0; l < Ls; ++l) {
         shr[8 * 8 + l] = inv[l];
         shr[8 * 8 + 8 + l] = tc[l];
-        tau[(size_t)l * n + c] = tc[l];
       }
       st<Ls>(qr, nn, (size_t)c * n + c, beta);
     }
@@ -286,7 +392,7 @@ __device__ void path_step(const BatchArgs &B, const PathMeta &pm, int p, double 
     }
     __syncthreads();
   }
-  // 5. reciprocals of diag(R), with the singularity test of the single-system path
+  // reciprocals of diag(R), with the singularity test of the single-system path
   {
     double dmax = 0.0;
     for (int i = tid; i < n; i += NT) dmax = fmax(dmax, fabs(qr[(size_t)i * n + i]));
@@ -304,7 +410,7 @@ __device__ void path_step(const BatchArgs &B, const PathMeta &pm, int p, double 
     }
   }
   __syncthreads();
-  // 6. M = R^{-1} Q^T: one wavefront per column, rows in lanes (p and p + 64)
+  // M = R^{-1} Q^T: one wavefront per column, rows in lanes (p and p + 64)
   {
     const int lane = tid & 63, wv = tid >> 6, nw = NT >> 6;
     for (int c = wv; c < n; c += nw) {
@@ -347,76 +453,154 @@ __device__ void path_step(const BatchArgs &B, const PathMeta &pm, int p, double 
     }
   }
   __syncthreads();
-  // 7. N = M A_1
-  if (D > 1)
-    for (int task = team; task < (int)nn; task += nteams) {
-      const int i = task / n, j = task - i * n;
-      double acc[Ls], s2[Ls];
-      md::zero<Ls>(acc);
-      for (int v = tl; v < n; v += T) {
-        double mv[Ls], av[Ls];
-        ld<Ls>(M, nn, (size_t)i * n + v, mv);
-        ld<Ls>(At, nnD, nn + (size_t)v * n + j, av);
-        MD<Ls>::fma_lazy(acc, mv, av);
-      }
-      team_sum_lazy<Ls>(acc, T);
-      MD<Ls>::renorm(acc, s2);
-      if (tl == 0) st<Ls>(N, nn, (size_t)i * n + j, s2);
+  if (tid == 0) flags[1] = sh_sing;
+}
+
+// 4. N = M A_1.
+template <int L, int Ls>
+__global__ void __launch_bounds__(BATCH_NT) batch_n_kernel(BatchArgs B) {
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  if (pm.D <= 1) return;
+  const int n = pm.n, T = B.tile[pm.bucket], nteams = blockDim.x / T, tl = threadIdx.x % T;
+  const size_t nn = (size_t)n * n, nnD = nn * pm.D;
+  for (int task = blockIdx.y * nteams + threadIdx.x / T; task < (int)nn; task += gridDim.y * nteams) {
+    const int i = task / n, j = task - i * n;
+    double acc[Ls], s2[Ls];
+    md::zero<Ls>(acc);
+    for (int v = tl; v < n; v += T) {
+      double mv[Ls], av[Ls];
+      ld<Ls>(w.M, nn, (size_t)i * n + v, mv);
+      ld<Ls>(w.At, nnD, nn + (size_t)v * n + j, av);
+      MD<Ls>::fma_lazy(acc, mv, av);
     }
-  // right-hand sides, coefficient-major r[k][i] (leading Ls limbs of b)
-  for (int q = tid; q < (int)nD; q += NT) {
-    const int i = q / D, s = q - i * D;
-#pragma unroll
-    for (int l = 0; l < Ls; ++l) r[(size_t)l * nD + (size_t)s * n + i] = b[(size_t)l * nD + q];
+    team_sum_lazy<Ls>(acc, T);
+    MD<Ls>::renorm(acc, s2);
+    if (tl == 0) st<Ls>(w.N, nn, (size_t)i * n + j, s2);
   }
-  __syncthreads();
-  // 8. stages
-  for (int k = 0; k < D; ++k) {
+}
+
+// 5. Stages in blocks of BATCH_BLOCK: the block's own stages by one workgroup
+// per path, dx_k = M r_k - N dx_{k-1} and r_m -= A_{m-k} dx_k for the later m of
+// the block (the term m = k + 1 is N dx_k) ...
+constexpr int BATCH_BLOCK = 4;
+
+template <int L, int Ls>
+__global__ void __launch_bounds__(512) batch_stages_kernel(BatchArgs B, int kb) {
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  const int n = pm.n, D = pm.D;
+  if (kb >= D) return;
+  const int T = B.tile[pm.bucket], nteams = blockDim.x / T, team = threadIdx.x / T, tl = threadIdx.x % T;
+  const size_t nn = (size_t)n * n, nD = (size_t)n * D, nnD = nn * D;
+  const int kend = min(kb + BATCH_BLOCK, D);
+  for (int k = kb; k < kend; ++k) {
     for (int i = team; i < n; i += nteams) {
       double acc[Ls], s2[Ls];
       md::zero<Ls>(acc);
       for (int v = tl; v < n; v += T) {
         double mv[Ls], rv[Ls];
-        ld<Ls>(M, nn, (size_t)i * n + v, mv);
-        ld<Ls>(r, nD, (size_t)k * n + v, rv);
+        ld<Ls>(w.M, nn, (size_t)i * n + v, mv);
+        ld<Ls>(w.r, nD, (size_t)k * n + v, rv);
         MD<Ls>::fma_lazy(acc, mv, rv);
         if (k > 0) {
           double nv[Ls], xv[Ls];
-          ld<Ls>(N, nn, (size_t)i * n + v, nv);
+          ld<Ls>(w.N, nn, (size_t)i * n + v, nv);
           md::neg<Ls>(nv, nv);
-          ld<Ls>(dx, nD, (size_t)(k - 1) * n + v, xv);
+          ld<Ls>(w.dx, nD, (size_t)(k - 1) * n + v, xv);
           MD<Ls>::fma_lazy(acc, nv, xv);
         }
       }
       team_sum_lazy<Ls>(acc, T);
       MD<Ls>::renorm(acc, s2);
-      if (tl == 0) st<Ls>(dx, nD, (size_t)k * n + i, s2);
+      if (tl == 0) st<Ls>(w.dx, nD, (size_t)k * n + i, s2);
     }
     __syncthreads();
-    // r_m -= A_{m-k} dx_k for m >= k + 2 (the term m = k + 1 is N dx_k)
-    const int ntask = (D - k - 2) * n;
+    const int ntask = (kend - k - 2) * n;
+    if (ntask <= 0) continue;
     for (int task = team; task < ntask; task += nteams) {
       const int mm = k + 2 + task / n, i = task % n;
       double acc[Ls], s2[Ls];
       md::zero<Ls>(acc);
       for (int v = tl; v < n; v += T) {
         double av[Ls], xv[Ls];
-        ld<Ls>(At, nnD, (size_t)(mm - k) * nn + (size_t)i * n + v, av);
-        ld<Ls>(dx, nD, (size_t)k * n + v, xv);
+        ld<Ls>(w.At, nnD, (size_t)(mm - k) * nn + (size_t)i * n + v, av);
+        ld<Ls>(w.dx, nD, (size_t)k * n + v, xv);
         MD<Ls>::fma_lazy(acc, av, xv);
       }
       team_sum_lazy<Ls>(acc, T);
       MD<Ls>::renorm(acc, s2);
       if (tl == 0) {
         double rv[Ls], t2[Ls];
-        ld<Ls>(r, nD, (size_t)mm * n + i, rv);
+        ld<Ls>(w.r, nD, (size_t)mm * n + i, rv);
         MD<Ls>::sub(rv, s2, t2);
-        st<Ls>(r, nD, (size_t)mm * n + i, t2);
+        st<Ls>(w.r, nD, (size_t)mm * n + i, t2);
       }
     }
     __syncthreads();
   }
-  // 9. x := x + dx, norms and status
+}
+
+// ... then all later right-hand sides, r_m -= sum over the block's stages k of
+// A_{m-k} dx_k, by the whole grid.  A task is a row of BATCH_BLOCK neighbouring
+// r_m: it reads 7 entries of A for 16 multiply-adds.
+template <int L, int Ls>
+__global__ void __launch_bounds__(BATCH_NT) batch_update_kernel(BatchArgs B, int kb) {
+  constexpr int K = BATCH_BLOCK;
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  const int n = pm.n, D = pm.D, first = kb + K;
+  if (first >= D) return;
+  const int T = B.tile[pm.bucket], nteams = blockDim.x / T, tl = threadIdx.x % T;
+  const size_t nn = (size_t)n * n, nD = (size_t)n * D, nnD = nn * D;
+  const int ntask = n * ((D - first + K - 1) / K);
+  for (int task = blockIdx.y * nteams + threadIdx.x / T; task < ntask; task += gridDim.y * nteams) {
+    const int g = task / n, i = task - g * n, m0 = first + K * g, a0 = m0 - kb - (K - 1);
+    double acc[K][Ls];
+#pragma unroll
+    for (int q = 0; q < K; ++q) md::zero<Ls>(acc[q]);
+    for (int v = tl; v < n; v += T) {
+      double dv[K][Ls];
+#pragma unroll
+      for (int q = 0; q < K; ++q) ld<Ls>(w.dx, nD, (size_t)(kb + q) * n + v, dv[q]);
+#pragma unroll
+      for (int a = 0; a < 2 * K - 1; ++a) {
+        const int ai = a0 + a;  // 1: in N
+        double av[Ls];
+        md::zero<Ls>(av);
+        if (ai > 1 && ai < D) ld<Ls>(w.At, nnD, (size_t)ai * nn + (size_t)i * n + v, av);
+#pragma unroll
+        for (int q = 0; q < K; ++q) {
+          const int s = q + K - 1 - a;  // stage of the block
+          if (s >= 0 && s < K) MD<Ls>::fma_lazy(acc[q], av, dv[s]);
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      double s2[Ls];
+      team_sum_lazy<Ls>(acc[q], T);
+      MD<Ls>::renorm(acc[q], s2);
+      if (tl == 0 && m0 + q < D) {
+        double rv[Ls], t2[Ls];
+        ld<Ls>(w.r, nD, (size_t)(m0 + q) * n + i, rv);
+        MD<Ls>::sub(rv, s2, t2);
+        st<Ls>(w.r, nD, (size_t)(m0 + q) * n + i, t2);
+      }
+    }
+  }
+}
+
+// 6. x := x + dx, norms and status.
+template <int L, int Ls>
+__global__ void __launch_bounds__(BATCH_NT) batch_finish_kernel(BatchArgs B) {
+  __shared__ double shr[BATCH_NT / 64];
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  const int tid = threadIdx.x, NT = blockDim.x, n = pm.n, D = pm.D, p = B.order[blockIdx.x];
+  const size_t nD = (size_t)n * D;
+  double *x = B.x + pm.x_off;
+  const double *b = w.b, *dx = w.dx;
   double nb = 0.0, nx = 0.0;
   bool finite = true;
   for (int q = tid; q < (int)nD; q += NT) {
@@ -439,45 +623,52 @@ __device__ void path_step(const BatchArgs &B, const PathMeta &pm, int p, double 
   if (tid == 0) {
     B.norms[2 * (size_t)p] = nb;
     B.norms[2 * (size_t)p + 1] = nx;
-    B.status[p] = sh_sing ? MD_ESINGULAR : (fin > 0.0 ? MD_ENONFINITE : MD_OK);
-  }
-  __syncthreads();
-}
-
-template <int L, int Ls>
-__global__ void __launch_bounds__(BATCH_NT) batch_step_kernel(BatchArgs B) {
-  extern __shared__ double lds[];
-  __shared__ double shr[8 * 8 + 16];
-  __shared__ int sh_idx, sh_sing;
-  double *slot = reinterpret_cast<double *>(B.slots + (size_t)blockIdx.x * B.slot_bytes);
-  while (true) {
-    if (threadIdx.x == 0) sh_idx = atomicAdd(B.queue, 1);
-    __syncthreads();
-    const int idx = sh_idx;
-    __syncthreads();
-    if (idx >= B.P) return;
-    const int p = B.order[idx];
-    const PathMeta pm = B.meta[p];
-    path_step<L, Ls>(B, pm, p, slot, lds, shr, sh_sing);
+    B.status[p] = path_need(w)[1] ? MD_ESINGULAR : (fin > 0.0 ? MD_ENONFINITE : MD_OK);
   }
 }
 
-__global__ void batch_reset_kernel(int *queue) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *queue = 0;
+template <int L, int Ls, int LIMBS, int G2>
+void launch_batch_eval(const BatchArgs &A, const int2 *work, int count, hipStream_t st) {
+  constexpr int lanes = (LIMBS == Ls ? 8 : 4) * G2, per = 8 * G2 < 64 ? 64 / lanes : 1;
+  const size_t lds = per * team_doubles<LIMBS, G2>() * sizeof(double);
+  hipLaunchKernelGGL((batch_eval_kernel<L, Ls, LIMBS, G2>), dim3((count + per - 1) / per), dim3(per * lanes), lds, st,
+                     A, work, count);
 }
 
-size_t batch_eval_lds_bytes(int L, int maxD) {
-  size_t best = 0;
-  for (int D = 1; D <= maxD; ++D) {
-    const size_t wpb = BATCH_NT / worker_lanes(D);
-    best = std::max(best, wpb * 3 * L * (D + 1) * sizeof(double));
+// cls = log2 G2
+template <int L, int Ls, int LIMBS>
+void launch_batch_eval(int cls, const BatchArgs &A, const int2 *work, int count, hipStream_t st) {
+  switch (cls) {
+    case 0: return launch_batch_eval<L, Ls, LIMBS, 1>(A, work, count, st);
+    case 1: return launch_batch_eval<L, Ls, LIMBS, 2>(A, work, count, st);
+    case 2: return launch_batch_eval<L, Ls, LIMBS, 4>(A, work, count, st);
+    case 3: return launch_batch_eval<L, Ls, LIMBS, 8>(A, work, count, st);
+    case 4: return launch_batch_eval<L, Ls, LIMBS, 16>(A, work, count, st);
+    case 5: return launch_batch_eval<L, Ls, LIMBS, 32>(A, work, count, st);
+    case 6: return launch_batch_eval<L, Ls, LIMBS, 64>(A, work, count, st);
   }
-  return best;
 }
 
 }  // namespace mdk
 
 // ------------------------------------------------------------------ host API
+
+constexpr int BATCH_CLASSES = 7;  // pair_lanes 1 .. 64
+
+// A run over a list of paths: chunks whose intermediates fit the workspace
+// together, and the monomials of a chunk by evaluation kernel, longest first.
+struct BatchRun {
+  struct Chunk {
+    int first, count;  // entries of order
+    int maxn, maxD;
+    int work[BATCH_CLASSES], works[BATCH_CLASSES];  // first, number
+  };
+  std::vector<Chunk> chunks;
+  void *d = nullptr;
+  const long long *off = nullptr;
+  const int2 *work = nullptr;
+  const int32_t *order = nullptr;
+};
 
 struct md_batch {
   int L, P, G;
@@ -489,7 +680,9 @@ struct md_batch {
   long long x_total, cff_total;
   size_t slot_bytes;
   mdk::PathMeta *d_meta = nullptr;
-  int32_t *d_order = nullptr, *d_tables = nullptr, *d_tile = nullptr;
+  int32_t *d_tables = nullptr, *d_tile = nullptr;
+  std::vector<int32_t> mon_ptr;           // host copy of the packed table
+  BatchRun run;                           // over all paths
   const int32_t *d_poly_ptr = nullptr, *d_mon_ptr = nullptr, *d_var = nullptr, *d_exp = nullptr;
   const int32_t *d_asm_ptr = nullptr, *d_asm_ent = nullptr;
   // one captured step (graph) for a fixed set of arguments
@@ -511,15 +704,111 @@ size_t slot_doubles(int L, int Ls, int n, int D, int m, int nnz) {
          3 * r((size_t)Ls * nn) + 2 * r((size_t)Ls * n) + r((size_t)Ls * nn) + 2 * r((size_t)Ls * nD);
 }
 
-// workspace: [queue (256 B)][G slots]
-size_t batch_ws_bytes(const md_batch *b) { return 256 + (size_t)b->G * b->slot_bytes; }
+// workspace: the intermediates of a chunk of paths, G times the largest path's
+size_t batch_ws_bytes(const md_batch *b) { return (size_t)b->G * b->slot_bytes; }
 
-hipError_t launch_step(const md_batch *b, int Ls, const int32_t *order, int P, const double *cff, const double *cst,
-                       double *x, int32_t *status, double *norms, void *ws, hipStream_t st) {
+// The chunks and work lists of a run over `list`, on the device.
+hipError_t build_run(const md_batch *b, const std::vector<int32_t> &list, BatchRun &run) {
+  const size_t budget = (size_t)b->G * b->slot_bytes;
+  std::vector<long long> off(list.size());
+  std::vector<int2> work;
+  size_t used = budget;  // the first path opens a chunk
+  auto cls = [&](int p) {
+    int c = 0;
+    while ((1 << c) < mdk::pair_lanes(b->meta[p].D)) ++c;
+    return c;
+  };
+  run.chunks.clear();
+  for (size_t q = 0; q < list.size(); ++q) {
+    const mdk::PathMeta &pm = b->meta[list[q]];
+    const size_t bytes = align256(slot_doubles(b->L, b->L, pm.n, pm.D, pm.m, pm.nnz) * sizeof(double));
+    if (used + bytes > budget) {
+      run.chunks.push_back({(int)q, 0, 0, 0, {}, {}});
+      used = 0;
+    }
+    off[q] = (long long)used;
+    used += bytes;
+    BatchRun::Chunk &ch = run.chunks.back();
+    ch.count++;
+    ch.maxn = std::max(ch.maxn, pm.n);
+    ch.maxD = std::max(ch.maxD, pm.D);
+  }
+  for (BatchRun::Chunk &ch : run.chunks)
+    for (int c = 0; c < BATCH_CLASSES; ++c) {
+      std::vector<std::vector<int2>> by_k(mdk::BATCH_MAXN + 1);  // by support size
+      for (int q = ch.first; q < ch.first + ch.count; ++q) {
+        if (cls(list[q]) != c) continue;
+        const mdk::PathMeta &pm = b->meta[list[q]];
+        const int32_t *mp = b->mon_ptr.data() + pm.mon_off;
+        for (int j = 0; j < pm.m; ++j) by_k[mp[j + 1] - mp[j]].push_back(make_int2(q, j));
+      }
+      ch.work[c] = (int)work.size();
+      for (int k = mdk::BATCH_MAXN; k >= 0; --k) work.insert(work.end(), by_k[k].begin(), by_k[k].end());
+      ch.works[c] = (int)work.size() - ch.work[c];
+    }
+  const size_t no = off.size() * sizeof(long long), nw = work.size() * sizeof(int2), nl = list.size() * sizeof(int32_t);
+  hipError_t e = hipMalloc(&run.d, no + nw + nl);
+  if (e != hipSuccess) return e;
+  char *d = static_cast<char *>(run.d);
+  if ((e = hipMemcpy(d, off.data(), no, hipMemcpyHostToDevice)) != hipSuccess ||
+      (nw && (e = hipMemcpy(d + no, work.data(), nw, hipMemcpyHostToDevice)) != hipSuccess) ||
+      (e = hipMemcpy(d + no + nw, list.data(), nl, hipMemcpyHostToDevice)) != hipSuccess) {
+    (void)hipFree(run.d);
+    run.d = nullptr;
+    return e;
+  }
+  run.off = reinterpret_cast<const long long *>(d);
+  run.work = reinterpret_cast<const int2 *>(d + no);
+  run.order = reinterpret_cast<const int32_t *>(d + no + nw);
+  return hipSuccess;
+}
+
+template <int L, int Ls>
+void launch_chunk(const mdk::BatchArgs &A, const BatchRun::Chunk &ch, const int2 *work, hipStream_t st) {
+  for (int c = BATCH_CLASSES - 1; c >= 0; --c) {
+    if (!ch.works[c]) continue;
+    mdk::launch_batch_eval<L, Ls, L>(c, A, work + ch.work[c], ch.works[c], st);
+    if constexpr (Ls != L) mdk::launch_batch_eval<L, Ls, Ls>(c, A, work + ch.work[c], ch.works[c], st);
+  }
+  using namespace mdk;
+  BatchArgs B = A;
+  B.order = A.order + ch.first;
+  B.off = A.off + ch.first;
+  const int P = ch.count, maxn = ch.maxn, maxD = ch.maxD;
+  // workgroups per path: enough to spread a chunk of few paths over the chip,
+  // few enough that small paths' empty workgroups do not count
+  const int Y = std::max(16, std::min(256, 2048 / P));
+  const dim3 NT(BATCH_NT), one(P), split(P, Y);
+  const size_t lds = (size_t)Ls * std::max(16 * 65, maxD > 64 ? 9 * maxD : 17 * maxD) * sizeof(double);
+  hipLaunchKernelGGL((batch_assemble_kernel<L, Ls>), split, NT, lds, st, B);
+  hipLaunchKernelGGL((batch_inv64_kernel<L, Ls, 1, 8, 4>), one, dim3(256), 0, st, B, 0);
+  if (maxn > 32) hipLaunchKernelGGL((batch_inv64_kernel<L, Ls, 1, 8, 8>), one, dim3(512), 0, st, B, 32);
+  if (maxn > 64) hipLaunchKernelGGL((batch_inv64_kernel<L, Ls, 2, 8, 16>), one, dim3(1024), 0, st, B, 64);
+  auto refine = [&](int lo, int hi) {
+    const int n = std::min(hi, maxn);
+    // rows enough to fill the chip without splitting a row's sums (1024 paths:
+    // 16.5 ms in four parts, 11.0 in one)
+    const int S = (long long)P * n >= 4096 ? 1 : refine_parts<Ls>(n);
+    hipLaunchKernelGGL((batch_refine_kernel<L, Ls>), dim3(P, n), dim3(64 * ((n + 63) / 64) * S), refine_lds<Ls>(n, S), st,
+                       B, lo, hi, S);
+  };
+  refine(0, 64);
+  if (maxn > 64) refine(64, 128);
+  hipLaunchKernelGGL((batch_factor_kernel<L, Ls>), one, NT, 0, st, B);
+  if (maxD > 1) hipLaunchKernelGGL((batch_n_kernel<L, Ls>), split, NT, 0, st, B);
+  for (int kb = 0; kb < maxD; kb += BATCH_BLOCK) {
+    hipLaunchKernelGGL((batch_stages_kernel<L, Ls>), one, dim3(512), 0, st, B, kb);
+    if (kb + BATCH_BLOCK < maxD) hipLaunchKernelGGL((batch_update_kernel<L, Ls>), split, NT, 0, st, B, kb);
+  }
+  hipLaunchKernelGGL((batch_finish_kernel<L, Ls>), one, NT, 0, st, B);
+}
+
+hipError_t launch_step(const md_batch *b, int Ls, const BatchRun &run, const double *cff, const double *cst, double *x,
+                       int32_t *status, double *norms, void *ws, hipStream_t st) {
   mdk::BatchArgs A;
-  A.P = P;
   A.meta = b->d_meta;
-  A.order = order;
+  A.order = run.order;
+  A.off = run.off;
   A.poly_ptr = b->d_poly_ptr;
   A.mon_ptr = b->d_mon_ptr;
   A.var = b->d_var;
@@ -534,19 +823,11 @@ hipError_t launch_step(const md_batch *b, int Ls, const int32_t *order, int P, c
   A.cff_ls = (size_t)b->cff_total;
   A.status = status;
   A.norms = norms;
-  A.queue = static_cast<int *>(ws);
-  A.slots = static_cast<char *>(ws) + 256;
-  A.slot_bytes = b->slot_bytes;
-  const size_t lds = mdk::batch_eval_lds_bytes(b->L, b->maxD);
-  const int G = std::min(b->G, P);
-  if (G <= 0) return hipSuccess;
-  hipLaunchKernelGGL(mdk::batch_reset_kernel, dim3(1), dim3(64), 0, st, A.queue);
-  if (b->L == 2) {
-    hipLaunchKernelGGL((mdk::batch_step_kernel<2, 2>), dim3(G), dim3(mdk::BATCH_NT), lds, st, A);
-  } else if (Ls == 4) {
-    hipLaunchKernelGGL((mdk::batch_step_kernel<4, 4>), dim3(G), dim3(mdk::BATCH_NT), lds, st, A);
-  } else {
-    hipLaunchKernelGGL((mdk::batch_step_kernel<4, 2>), dim3(G), dim3(mdk::BATCH_NT), lds, st, A);
+  A.slots = static_cast<char *>(ws);
+  for (const BatchRun::Chunk &ch : run.chunks) {
+    if (b->L == 2) launch_chunk<2, 2>(A, ch, run.work, st);
+    else if (Ls == 4) launch_chunk<4, 4>(A, ch, run.work, st);
+    else launch_chunk<4, 2>(A, ch, run.work, st);
   }
   return hipGetLastError();
 }
@@ -657,6 +938,7 @@ int md_batch_create(int prec, int npaths, const int32_t *n, const int32_t *d, co
   }
   b->x_total = xo;
   b->cff_total = co;
+  b->mon_ptr = tab_mon;
   b->order.resize(npaths);
   std::iota(b->order.begin(), b->order.end(), 0);
   std::stable_sort(b->order.begin(), b->order.end(), [&](int a2, int b2) { return b->cost[a2] > b->cost[b2]; });
@@ -677,14 +959,14 @@ int md_batch_create(int prec, int npaths, const int32_t *n, const int32_t *d, co
   const size_t nt = tab_poly.size() + tab_mon.size() + tab_var.size() + tab_exp.size() + tab_asm.size() +
                     tab_asment.size();
   std::vector<int32_t> all;
-  all.reserve(nt + npaths + mdk::BATCH_BUCKETS);
+  all.reserve(nt + mdk::BATCH_BUCKETS);
   auto seg = [&](const std::vector<int32_t> &v) {
     size_t o = all.size();
     all.insert(all.end(), v.begin(), v.end());
     return o;
   };
   const size_t o_poly = seg(tab_poly), o_mon = seg(tab_mon), o_var = seg(tab_var), o_exp = seg(tab_exp),
-               o_asm = seg(tab_asm), o_ase = seg(tab_asment), o_ord = seg(b->order);
+               o_asm = seg(tab_asm), o_ase = seg(tab_asment);
   std::vector<int32_t> tl(b->tile, b->tile + mdk::BATCH_BUCKETS);
   const size_t o_tile = seg(tl);
   if ((e = hipMalloc((void **)&b->d_tables, std::max<size_t>(all.size(), 1) * sizeof(int32_t))) != hipSuccess ||
@@ -692,7 +974,9 @@ int md_batch_create(int prec, int npaths, const int32_t *n, const int32_t *d, co
       (e = hipMalloc((void **)&b->d_meta, b->meta.size() * sizeof(mdk::PathMeta))) != hipSuccess ||
       (e = hipMemcpy(b->d_meta, b->meta.data(), b->meta.size() * sizeof(mdk::PathMeta), hipMemcpyHostToDevice)) !=
           hipSuccess ||
+      (e = build_run(b, b->order, b->run)) != hipSuccess ||
       (e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking)) != hipSuccess) {
+    if (b->run.d) (void)hipFree(b->run.d);
     if (b->d_tables) (void)hipFree(b->d_tables);
     if (b->d_meta) (void)hipFree(b->d_meta);
     delete b;
@@ -704,19 +988,7 @@ int md_batch_create(int prec, int npaths, const int32_t *n, const int32_t *d, co
   b->d_exp = b->d_tables + o_exp;
   b->d_asm_ptr = b->d_tables + o_asm;
   b->d_asm_ent = b->d_tables + o_ase;
-  b->d_order = b->d_tables + o_ord;
   b->d_tile = b->d_tables + o_tile;
-  static bool attr = false;
-  if (!attr) {  // dynamic LDS of the evaluation workers above 64 KB needs the attribute
-    (void)hipFuncSetAttribute((const void *)mdk::batch_step_kernel<2, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              150 * 1024);
-    (void)hipFuncSetAttribute((const void *)mdk::batch_step_kernel<4, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              150 * 1024);
-    (void)hipFuncSetAttribute((const void *)mdk::batch_step_kernel<4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              150 * 1024);
-    (void)hipGetLastError();
-    attr = true;
-  }
   *out = b;
   return MD_OK;
 }
@@ -725,6 +997,7 @@ int md_batch_destroy(md_batch *b) {
   if (!b) return MD_OK;
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->cap) (void)hipStreamDestroy(b->cap);
+  if (b->run.d) (void)hipFree(b->run.d);
   if (b->d_tables) (void)hipFree(b->d_tables);
   if (b->d_meta) (void)hipFree(b->d_meta);
   delete b;
@@ -768,7 +1041,7 @@ int md_batch_newton_step(md_batch *b, int prec_solve, const double *cff, const d
     hipGraph_t g = nullptr;
     if ((e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal)) != hipSuccess)
       return mdk::api_hip_fail(e, "capture");
-    hipError_t le = launch_step(b, prec_solve, b->d_order, b->P, cff, cst, x, dev_status, dev_norms, ws, b->cap);
+    hipError_t le = launch_step(b, prec_solve, b->run, cff, cst, x, dev_status, dev_norms, ws, b->cap);
     e = hipStreamEndCapture(b->cap, &g);
     if (le != hipSuccess || e != hipSuccess) {
       if (g) (void)hipGraphDestroy(g);
@@ -790,7 +1063,7 @@ int md_batch_newton_step(md_batch *b, int prec_solve, const double *cff, const d
   for (int q = 0; q < 8; ++q) b->key[q] = key[q];
   b->key_prec = prec_solve;
   b->seen = true;
-  e = launch_step(b, prec_solve, b->d_order, b->P, cff, cst, x, dev_status, dev_norms, ws, st);
+  e = launch_step(b, prec_solve, b->run, cff, cst, x, dev_status, dev_norms, ws, st);
   return e == hipSuccess ? MD_OK : mdk::api_hip_fail(e, "batched step");
 }
 
@@ -805,16 +1078,15 @@ int md_batch_autotune(md_batch *b, int prec_solve, const double *cff, const doub
   const size_t xbytes = (size_t)b->L * b->x_total * sizeof(double);
   hipError_t e;
   hipEvent_t e0 = nullptr, e1 = nullptr;
-  int32_t *d_list = nullptr;
-  if ((e = hipEventCreate(&e0)) != hipSuccess || (e = hipEventCreate(&e1)) != hipSuccess ||
-      (e = hipMalloc((void **)&d_list, (size_t)b->P * sizeof(int32_t))) != hipSuccess)
+  if ((e = hipEventCreate(&e0)) != hipSuccess || (e = hipEventCreate(&e1)) != hipSuccess)
     return mdk::api_hip_fail(e, "autotune setup");
   for (int bk = 0; bk < mdk::BATCH_BUCKETS; ++bk) {
     std::vector<int32_t> list;
     for (int32_t p : b->order)
       if (b->meta[p].bucket == bk) list.push_back(p);
     if (list.empty()) continue;
-    if ((e = hipMemcpy(d_list, list.data(), list.size() * sizeof(int32_t), hipMemcpyHostToDevice)) != hipSuccess) break;
+    BatchRun run;
+    if ((e = build_run(b, list, run)) != hipSuccess) break;
     float best = 0.0f;
     int best_t = b->tile[bk];
     for (int c = 0; c < 3 && e == hipSuccess; ++c) {
@@ -826,8 +1098,7 @@ int md_batch_autotune(md_batch *b, int prec_solve, const double *cff, const doub
       for (int rep = 0; rep < 2 && e == hipSuccess; ++rep) {  // the first run warms up
         if ((e = hipMemcpyAsync(x_scratch, x, xbytes, hipMemcpyDeviceToDevice, st)) != hipSuccess) break;
         if ((e = hipEventRecord(e0, st)) != hipSuccess) break;
-        if ((e = launch_step(b, prec_solve, d_list, (int)list.size(), cff, cst, x_scratch, dev_status, dev_norms, ws,
-                             st)) != hipSuccess)
+        if ((e = launch_step(b, prec_solve, run, cff, cst, x_scratch, dev_status, dev_norms, ws, st)) != hipSuccess)
           break;
         if ((e = hipEventRecord(e1, st)) != hipSuccess || (e = hipEventSynchronize(e1)) != hipSuccess) break;
         if ((e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess) break;
@@ -838,12 +1109,13 @@ int md_batch_autotune(md_batch *b, int prec_solve, const double *cff, const doub
       }
     }
     b->tile[bk] = best_t;
+    (void)hipStreamSynchronize(st);  // (a failed launch may leave others behind)
+    (void)hipFree(run.d);
   }
   if (e == hipSuccess)
     e = hipMemcpy(const_cast<int32_t *>(b->d_tile), b->tile, sizeof(b->tile), hipMemcpyHostToDevice);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  (void)hipFree(d_list);
   if (e != hipSuccess) return mdk::api_hip_fail(e, "autotune");
   if (chosen)
     for (int q = 0; q < mdk::BATCH_BUCKETS; ++q) chosen[q] = b->tile[q];

@@ -31,299 +31,6 @@
 
 namespace mdk {
 
-// Two teams of lanes per monomial.  Team B forms the backward chain while team
-// A forms the common factor; then at every forward step A forms f_j = f_{j-1} *
-// x_{v_j} while B forms the cross product f_{j-1} * b_{k-j} of the same f_{j-1},
-// so the chain of dependent products shortens from 3k - 5 to about 2k - 2
-// (values only: team A alone).
-//
-// Within a product the outputs are paired, o1 = p and o2 = D-1-p, and the D+1
-// terms of a pair, those of o2 first, are split over four lanes (quarters) of
-// the team's 4 G2, G2 = pair_lanes: the chain of a product is a quarter of a
-// pair's terms, and only the last two quarters change from o2 to o1.  The
-// quarters' level sums are added pairwise; the lanes of quarter 0 (o2) and
-// quarter 3 (o1) finish one coefficient each, which they keep in registers
-// from product to product.  U (the f of the forward chain, B's chain ahead of
-// it) and V are in LDS, a stride known at compile time apart, with entry D
-// zero for masked terms.
-//
-// Orders up to 8 leave room for several monomials in a wavefront.
-//
-// Bound by the FP64 issue rate (quad double, 2048 monomials, order 64: 230 us,
-// 128 for the multiply-adds alone) and, in small systems, by the longest
-// monomial's chain.  Against one wavefront per team (orders 33 and up) and one
-// worker per monomial (below), in us: quad double 2048 monomials of order 64
-// 243 -> 230, 1463 of order 51 150 -> 101, 1024 of order 32 130 -> 49, 2048
-// of order 1 54 -> 25; double double 2048 of order 64 97 -> 52, 64 of order 16
-// 14 -> 8.
-template <int G2> struct TeamLane {
-  int D, quarter, p, o1, o2;
-  int own;     // the coefficient the lane finishes, or -1
-  int t0, t1;  // the lane's terms
-};
-
-template <int G2>
-__device__ __forceinline__ TeamLane<G2> team_lane(int D, int tl) {
-  TeamLane<G2> q;
-  q.D = D;
-  q.quarter = tl / G2;
-  q.p = tl - q.quarter * G2;
-  q.o1 = min(q.p, (D - 1) / 2);  // (lanes without a pair repeat the last one)
-  q.o2 = D - 1 - q.o1;
-  q.own = q.p > q.o1 ? -1 : q.quarter == 0 ? q.o2 : (q.quarter == 3 && q.o2 > q.o1) ? q.o1 : -1;
-  // o2 has at least half = ceil((D + 1) / 2) terms
-  const int half = (D + 2) / 2, h0 = (half + 1) / 2, h1 = half + (D + 2 - half) / 2;
-  q.t0 = q.quarter == 0 ? 0 : q.quarter == 1 ? h0 : q.quarter == 2 ? half : h1;
-  q.t1 = q.quarter == 0 ? h0 : q.quarter == 1 ? half : q.quarter == 2 ? h1 : D + 1;
-  return q;
-}
-
-// Workgroup barrier; one wavefront needs none of its own.
-template <bool WIDE>
-__device__ __forceinline__ void team_sync() {
-  if constexpr (WIDE) __syncthreads();
-  else wave_sync();
-}
-
-// The level sums of the lane's terms of U V: part2 of output o2, part1 of o1.
-template <int L, int G2>
-__device__ __forceinline__ void team_conv(const double *U, const double *V, const TeamLane<G2> &q, double (&part1)[L],
-                                          double (&part2)[L]) {
-  constexpr int Dp = 2 * G2 + 1;
-  double acc[L], parked[L];
-  md::zero<L>(acc);
-  md::zero<L>(parked);
-  const int H = ((q.D + 2) / 2 + 1) / 2;  // terms of quarter 0; the others have as many or one less
-  const bool ahead = q.t0 <= q.o2;
-  const int i0 = ahead ? q.t0 : q.t0 - q.o2 - 1;
-  const double *pu = U + i0, *pv = V + ((ahead ? q.o2 : q.o1) - i0), *const pv1 = V + q.o1;
-  auto term = [&] {
-    double u[L], v[L];
-#pragma unroll
-    for (int l = 0; l < L; ++l) {
-      u[l] = pu[l * Dp];
-      v[l] = pv[l * Dp];
-    }
-    MD<L>::fma_lazy(acc, u, v);
-  };
-  const int park = q.o2 - q.t0;  // o2's last term
-  auto advance = [&](int tt) {
-    const bool change = tt == park;
-    pu = change ? U : pu + 1;
-    pv = change ? pv1 : pv - 1;
-    if (__any(change)) {
-      if (change) {
-        md::copy<L>(acc, parked);
-        md::zero<L>(acc);
-      }
-    }
-  };
-  int tt = 0;
-  for (; tt + 2 < H; tt += 2) {
-    term();
-    advance(tt);
-    term();
-    advance(tt + 1);
-  }
-  if (tt + 1 < H) {
-    term();
-    advance(tt);
-  }
-  if (q.t1 - q.t0 < H) {
-    pu = U + q.D;
-    pv = V;
-  }
-  term();
-  const bool changed = park < H - 1;  // the lane ended on o1
-#pragma unroll
-  for (int l = 0; l < L; ++l) {
-    part2[l] = changed ? parked[l] : acc[l];
-    part1[l] = changed ? acc[l] : 0.0;
-  }
-}
-
-// LDS of one monomial: U and V of both teams, then per team the exchange of
-// partial sums.
-template <int L, int G2>
-constexpr size_t team_doubles() {
-  return (size_t)(4 * (2 * G2 + 1) + 2 * (G2 > 32 ? 4 : G2 > 16 ? 1 : 0) * G2) * L;
-}
-
-template <int L, int G2>
-__device__ void eval_monomial_team(const EvalArgs &a, int mono, int tid, double *lds) {
-  constexpr int TL = 4 * G2, Dp = 2 * G2 + 1;
-  constexpr bool WIDE = 2 * TL > 64, ALONE = 2 * TL >= 64;  // ALONE: one monomial per workgroup
-  const int Dc = a.Dc, D = a.D;
-  const bool derivs = a.values_only == 0;
-  const bool isA = tid < TL;
-  const int team = isA ? 0 : 1, tl = tid - team * TL;
-  const TeamLane<G2> q = team_lane<G2>(Dc, tl);
-  const bool owner = q.own >= 0;
-  const int s = owner ? q.own : 0;
-  double *UA = lds;
-  double *Uown = lds + team * 2 * L * Dp, *V = Uown + L * Dp;
-  double *X = lds + 4 * L * Dp + team * (G2 > 32 ? 4 : 1) * G2 * L;
-  for (int r = tl; r < 4 * L; r += TL) lds[r * Dp + Dc] = 0.0;
-  int e0 = a.mon_ptr[mono], e1 = a.mon_ptr[mono + 1];
-  if constexpr (ALONE) {
-    e0 = __builtin_amdgcn_readfirstlane(e0);
-    e1 = __builtin_amdgcn_readfirstlane(e1);
-  }
-  const int k = e1 - e0;
-  const size_t nD = (size_t)a.n * D, mD = (size_t)a.m * D, zD = (size_t)a.nnz * D;
-  const size_t xls = a.x_ls ? a.x_ls : nD;
-  double c[L];
-  ld<L>(a.cff, a.cff_ls ? a.cff_ls : (size_t)a.m, mono, c);
-  if (k == 0) {  // constant monomial (all of its lanes leave)
-    if (isA && owner) {
-#pragma unroll
-      for (int l = 0; l < L; ++l) a.val[(size_t)l * mD + (size_t)mono * D + s] = (s == 0) ? c[l] : 0.0;
-      if (a.vsize) a.vsize[(size_t)mono * D + s] = (s == 0) ? fabs(c[0]) : 0.0;
-    }
-    return;
-  }
-  // this lane's coefficient of a series in memory; zero for lanes without one
-  auto load = [&](const double *g, size_t ls, size_t off, double (&r)[L]) {
-    md::zero<L>(r);
-    if (owner) ld<L>(g, ls, off + s, r);
-  };
-  auto load_x = [&](int e, double (&r)[L]) { load(a.x, xls, (size_t)a.var[e0 + e] * D, r); };
-  auto put = [&](double *W, const double (&r)[L]) {
-    if (owner) {
-#pragma unroll
-      for (int l = 0; l < L; ++l) W[l * Dp + s] = r[l];
-    }
-  };
-  auto store_der = [&](int e, const double (&r)[L]) {
-    if (owner) st<L>(a.der, zD, (size_t)(e0 + e) * D + s, r);
-  };
-
-  int nbig = 0;
-  for (int j = 0; j < k; ++j) nbig += a.exp[e0 + j] >= 2 ? 1 : 0;
-  const bool f0_scalar = nbig == 0;
-  // steps: the common factor CF = prod x^(a-1) (A) beside the backward chain
-  // b_q, q = 2..k-1, parked in the slot of entry k-q-1 (B), then the forward
-  // chain (A) beside the cross products (B)
-  const int steps_a = max(nbig - 1, 0), steps_b = derivs ? max(k - 2, 0) : 0;
-  const int start = max(steps_a, steps_b), total = start + k;
-  double f[L];  // f_j (A), b_q (B)
-  md::zero<L>(f);
-  int next = 0;  // entry of the next factor of CF
-  auto load_cf = [&](double (&w)[L]) {
-    while (a.exp[e0 + next] < 2) ++next;
-    const int p = a.exp[e0 + next] - 1, v = a.var[e0 + next];
-    ++next;
-    if (p == 1) load(a.x, xls, (size_t)v * D, w);
-    else load(a.pw + (size_t)(p - 2) * L * nD, nD, (size_t)v * D, w);
-  };
-  if (isA && !f0_scalar) load_cf(f);
-  if (!isA && steps_b > 0) load_x(k - 1, f);  // b_1
-  const bool track = a.vsize != nullptr;
-  double vmax = 0.0;
-  for (int t = 0; t < total; ++t) {
-    const int j = t - start + 1;  // forward step (from 1), else an earlier one
-    const int ej = j - 1, aj = j >= 1 ? a.exp[e0 + ej] : 1;
-    if (j == 1 && isA) {  // f_0 = c CF (c in coefficient 0 without a common factor)
-      if (!f0_scalar) {
-        double w[L];
-        MD<L>::mul(c, f, w);
-        md::copy<L>(w, f);
-      } else {
-#pragma unroll
-        for (int l = 0; l < L; ++l) f[l] = s == 0 ? c[l] : 0.0;
-      }
-      vmax = fabs(f[0]);
-    }
-    const bool scalar = f0_scalar && j == 1;
-    const bool run = j < 1 ? t < (isA ? steps_a : steps_b) : (isA || j < k);
-    double r[L];
-    if (run) {  // the operand V
-      double w[L];
-      if (j < 1) {
-        if (isA) load_cf(w);
-        else load_x(k - 2 - t, w);  // x_{v_{k-q+1}}, q - 2 = t
-      } else if (isA) {
-        load_x(ej, w);
-      } else if (k - j == 1) {
-        load_x(k - 1, w);  // b_1 = x_{v_k}
-      } else {
-        load(a.der, zD, (size_t)(e0 + ej) * D, w);  // b_{k-j}, which this lane stored
-      }
-      if (scalar) MD<L>::mul(c, w, r);
-      else put(V, w);
-      if ((isA || j < 1) && !scalar) put(Uown, f);
-    }
-    if (isA && derivs && j == k) {  // d/dx_{v_k} = a_k f_{k-1}
-      double w[L];
-      md::copy<L>(f, w);
-      md::mul_int<L>(w, aj);
-      store_der(ej, w);
-    }
-    if (!scalar) {  // r = U V, this lane's coefficient; U and V are free afterwards
-      team_sync<WIDE>();
-      double mine[L], send[L];
-      if (run) {
-        team_conv<L, G2>(j < 1 ? Uown : UA, V, q, send, mine);
-        // quarters 0, 1, 2 go on with o2, quarter 3 with o1
-#pragma unroll
-        for (int l = 0; l < L; ++l) {
-          const double p1 = send[l], p2 = mine[l];
-          mine[l] = q.quarter == 3 ? p1 : p2;
-          send[l] = q.quarter == 2 ? p1 : p2;
-        }
-      } else {
-        md::zero<L>(mine);
-        md::zero<L>(send);
-      }
-      double o[L];
-      if constexpr (G2 <= 32) {
-#pragma unroll
-        for (int l = 0; l < L; ++l) o[l] = __shfl_xor(send[l], G2, 64);
-      } else {
-        if (q.quarter > 0) {
-#pragma unroll
-          for (int l = 0; l < L; ++l) X[(q.quarter * L + l) * G2 + q.p] = send[l];
-        }
-        team_sync<WIDE>();
-#pragma unroll
-        for (int l = 0; l < L; ++l) o[l] = q.quarter == 1 ? 0.0 : X[((q.quarter ^ 1) * L + l) * G2 + q.p];
-      }
-      MD<L>::add_lazy(mine, o);
-      if constexpr (G2 <= 16) {
-#pragma unroll
-        for (int l = 0; l < L; ++l) o[l] = __shfl_xor(mine[l], 2 * G2, 64);
-        team_sync<WIDE>();
-      } else {
-        if (q.quarter == 2) {
-#pragma unroll
-          for (int l = 0; l < L; ++l) X[l * G2 + q.p] = mine[l];
-        }
-        team_sync<WIDE>();
-#pragma unroll
-        for (int l = 0; l < L; ++l) o[l] = X[l * G2 + q.p];
-      }
-      if (q.quarter == 0) MD<L>::add_lazy(mine, o);
-      MD<L>::renorm(mine, r);
-    }
-    if (isA) {
-      if (run) md::copy<L>(r, f);
-      if (j >= 1) vmax = fmax(vmax, fabs(f[0]));
-    } else if (run) {
-      if (j < 1) {
-        md::copy<L>(r, f);
-        store_der(k - 3 - t, r);
-      } else {
-        md::mul_int<L>(r, aj);
-        store_der(ej, r);
-      }
-    }
-  }
-  if (isA && owner) {
-    st<L>(a.val, mD, (size_t)mono * D + s, f);
-    if (track) a.vsize[(size_t)mono * D + s] = vmax;
-  }
-}
-
 template <int L, int G2>
 __global__ void __launch_bounds__((8 * G2 > 64 ? 8 * G2 : 64), L == 8 ? 2 : 4) evaldiff_team_kernel(EvalArgs a) {
   extern __shared__ __align__(16) double lds[];
