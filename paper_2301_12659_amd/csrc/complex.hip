@@ -7,7 +7,10 @@
 // product W = U * V is, per coefficient s,
 //     Re W_s = sum_i Re U_i Re V_{s-i} - Im U_i Im V_{s-i},
 //     Im W_s = sum_i Re U_i Im V_{s-i} + Im U_i Re V_{s-i},
-// the four real products of the 4M method.  A complex worker has 2G lanes:
+// the four real products of the 4M method.  In double and quad doubles a
+// monomial has two teams of lanes as in the real evaluation, each of them once
+// per part (eval_monomial_team_c); a lane adds both of its part's products into
+// one level-sum accumulator.  In octo doubles a complex worker has 2G lanes:
 // lanes [0, G) form the real part and lanes [G, 2G) the imaginary part of
 // every output at the same time, each lane adding both of its part's products
 // into one level-sum accumulator, with the term layout of the real
@@ -258,6 +261,221 @@ __device__ void eval_monomial_c(const EvalArgs &a, int mono, int lane2, int G, d
   store_c(a.val, mD, vp, (size_t)mono * D, U, L, Dc, lane2, G2L);
 }
 
+// A term of one part of a complex product, pu and pv at the real part of U and
+// the lane's part of V: part 0 adds Re U Re V - Im U Im V, part 1
+// Re U Im V + Im U Re V.
+template <int L, int G2> struct TeamTermC {
+  int other;   // from the lane's part of V to the other part
+  double sgn;  // of the second product
+  __device__ __forceinline__ void operator()(const double *pu, const double *pv, double (&acc)[L]) const {
+    constexpr int Dp = 2 * G2 + 1;
+    double u[L], v[L];
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      u[l] = pu[l * Dp];
+      v[l] = pv[l * Dp];
+    }
+    MD<L>::fma_lazy(acc, u, v);
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      u[l] = sgn * pu[(L + l) * Dp];
+      v[l] = pv[other + l * Dp];
+    }
+    MD<L>::fma_lazy(acc, u, v);
+  }
+};
+
+// One complex monomial by two teams of lanes (evaldiff_dev.hpp), each of them
+// a real team per part: 16 G2 lanes, and every lane finishes one coefficient
+// of its part.  U and V in LDS are complex series [2][L][Dp].  Bound by the FP64
+// issue rate: 2048 quad-double monomials of order 64 in 699 us (860 with one
+// worker of two wavefronts per monomial), 512 for the multiply-adds alone.
+template <int L, int G2>
+constexpr size_t team_doubles_c() {
+  return (size_t)8 * (2 * G2 + 1) * L + 4 * team_exchange<L, G2>();
+}
+
+template <int L, int G2>
+__device__ void eval_monomial_team_c(const EvalArgs &a, int mono, int tid, double *lds) {
+  constexpr int TL = 4 * G2, Dp = 2 * G2 + 1, CS = 2 * L * Dp;
+  constexpr bool WIDE = 4 * TL > 64, ALONE = 4 * TL >= 64;
+  const int Dc = a.Dc, D = a.D;
+  const int group = tid / TL, tl = tid - group * TL, part = group & 1;
+  const bool isA = group < 2;
+  const TeamLane<G2> q = team_lane<G2>(Dc, tl);
+  const bool owner = q.own >= 0;
+  const int s = owner ? q.own : 0;
+  double *UA = lds, *Uown = lds + (isA ? 0 : 2 * CS), *V = Uown + CS;
+  double *X = lds + 4 * CS + group * team_exchange<L, G2>();
+  for (int r = tid; r < 8 * L; r += 4 * TL) lds[r * Dp + Dc] = 0.0;
+  int e0 = a.mon_ptr[mono], e1 = a.mon_ptr[mono + 1];
+  if constexpr (ALONE) {
+    e0 = __builtin_amdgcn_readfirstlane(e0);
+    e1 = __builtin_amdgcn_readfirstlane(e1);
+  }
+  const int k = e1 - e0;
+  const size_t nD = (size_t)a.n * D, mD = (size_t)a.m * D, zD = (size_t)a.nnz * D;
+  const size_t xp = (size_t)L * nD, vp = (size_t)L * mD, dp = (size_t)L * zD, cp = (size_t)L * a.m;
+  // one part of the coefficient
+  auto coefficient = [&](int pt, double (&r)[L]) { ld<L>(a.cff + pt * cp, (size_t)a.m, mono, r); };
+  if (k == 0) {  // constant monomial (all of its lanes leave)
+    if (isA && owner) {
+      double c[L];
+      coefficient(part, c);
+#pragma unroll
+      for (int l = 0; l < L; ++l)
+        a.val[part * vp + (size_t)l * mD + (size_t)mono * D + s] = (s == 0) ? c[l] : 0.0;
+    }
+    return;
+  }
+  // this lane's coefficient of the own or the other part of a series in
+  // memory; zero for lanes without one
+  auto load = [&](const double *g, size_t ls, size_t plane, size_t off, int pt, double (&r)[L]) {
+    md::zero<L>(r);
+    if (owner) ld<L>(g + pt * plane, ls, off + s, r);
+  };
+  auto load_x = [&](int e, int pt, double (&r)[L]) { load(a.x, nD, xp, (size_t)a.var[e0 + e] * D, pt, r); };
+  auto put = [&](double *W, const double (&r)[L]) {
+    if (owner) {
+#pragma unroll
+      for (int l = 0; l < L; ++l) W[(part * L + l) * Dp + s] = r[l];
+    }
+  };
+  auto store_der = [&](int e, const double (&r)[L]) {
+    if (owner) st<L>(a.der + part * dp, zD, (size_t)(e0 + e) * D + s, r);
+  };
+  // c w for a series with the lane's part own and the other part oth
+  auto times_c = [&](const double (&own)[L], const double (&oth)[L], double (&r)[L]) {
+    double acc[L], c[L];
+    md::zero<L>(acc);
+    coefficient(0, c);
+    MD<L>::fma_lazy(acc, c, own);
+    coefficient(1, c);
+    if (!part) md::neg<L>(c, c);
+    MD<L>::fma_lazy(acc, c, oth);
+    MD<L>::renorm(acc, r);
+  };
+
+  int nbig = 0;
+  for (int j = 0; j < k; ++j) nbig += a.exp[e0 + j] >= 2 ? 1 : 0;
+  const bool f0_scalar = nbig == 0;
+  // the steps of eval_monomial_team; exponents of at most two
+  const int steps_a = max(nbig - 1, 0), steps_b = max(k - 2, 0);
+  const int start = max(steps_a, steps_b), total = start + k;
+  double f[L];  // f_j (A), b_q (B)
+  md::zero<L>(f);
+  int next = 0;  // entry of the next factor of the common factor
+  auto load_cf = [&](double (&w)[L]) {
+    while (a.exp[e0 + next] < 2) ++next;
+    load_x(next, part, w);
+    ++next;
+  };
+  if (isA && !f0_scalar) load_cf(f);
+  if (!isA && steps_b > 0) load_x(k - 1, part, f);  // b_1
+  for (int t = 0; t < total; ++t) {
+    const int j = t - start + 1;  // forward step (from 1), else an earlier one
+    const int ej = j - 1, aj = j >= 1 ? a.exp[e0 + ej] : 1;
+    if (j == 1) {  // f_0 = c CF (c in coefficient 0 without a common factor)
+      if (isA && !f0_scalar) put(UA, f);
+      team_sync<WIDE>();  // (also: team B reads the parked products, which the other part's lanes stored)
+      if (isA && !f0_scalar) {
+        double oth[L], w[L];
+#pragma unroll
+        for (int l = 0; l < L; ++l) oth[l] = UA[((1 - part) * L + l) * Dp + s];
+        times_c(f, oth, w);
+        md::copy<L>(w, f);
+      } else if (isA) {
+        coefficient(part, f);
+#pragma unroll
+        for (int l = 0; l < L; ++l) f[l] = s == 0 ? f[l] : 0.0;
+      }
+      team_sync<WIDE>();
+    }
+    const bool scalar = f0_scalar && j == 1;
+    const bool run = j < 1 ? t < (isA ? steps_a : steps_b) : (isA || j < k);
+    double r[L];
+    if (run) {  // the operand V
+      double w[L];
+      auto operand = [&](int pt, double (&y)[L]) {
+        if (isA) load_x(ej, pt, y);
+        else if (k - j == 1) load_x(k - 1, pt, y);  // b_1 = x_{v_k}
+        else load(a.der, zD, dp, (size_t)(e0 + ej) * D, pt, y);  // b_{k-j}
+      };
+      if (j >= 1) operand(part, w);
+      else if (isA) load_cf(w);
+      else load_x(k - 2 - t, part, w);  // x_{v_{k-q+1}}, q - 2 = t
+      if (scalar) {
+        double oth[L];
+        operand(1 - part, oth);
+        times_c(w, oth, r);
+      } else {
+        put(V, w);
+      }
+      if ((isA || j < 1) && !scalar) put(Uown, f);
+    }
+    if (isA && j == k) {  // d/dx_{v_k} = a_k f_{k-1}
+      double w[L];
+      md::copy<L>(f, w);
+      md::mul_int<L>(w, aj);
+      store_der(ej, w);
+    }
+    if (scalar) {
+      // the cross product takes the slot that the other part's lanes read
+      team_sync<WIDE>();
+    } else {  // r = U V, this lane's coefficient; U and V are free afterwards
+      team_sync<WIDE>();
+      double part1[L], part2[L];
+      if (run) {
+        team_conv<L, G2>(j < 1 ? Uown : UA, V + part * (CS / 2), q,
+                         TeamTermC<L, G2>{part ? -(CS / 2) : CS / 2, part ? 1.0 : -1.0}, part1, part2);
+      } else {
+        md::zero<L>(part1);
+        md::zero<L>(part2);
+      }
+      team_sum<L, G2, WIDE>(q, X, part1, part2, r);
+    }
+    if (isA) {
+      if (run) md::copy<L>(r, f);
+    } else if (run) {
+      if (j < 1) {
+        md::copy<L>(r, f);
+        store_der(k - 3 - t, r);
+      } else {
+        md::mul_int<L>(r, aj);
+        store_der(ej, r);
+      }
+    }
+  }
+  if (isA && owner) st<L>(a.val + part * vp, mD, (size_t)mono * D + s, f);
+}
+
+template <int L, int G2>
+__global__ void __launch_bounds__((16 * G2 > 64 ? 16 * G2 : 64), 4) evaldiff_team_complex_kernel(EvalArgs a) {
+  extern __shared__ __align__(16) double lds[];
+  if constexpr (16 * G2 >= 64) {
+    eval_monomial_team_c<L, G2>(a, __builtin_amdgcn_readfirstlane(a.order[blockIdx.x]), threadIdx.x, lds);
+  } else {  // several monomials per wavefront
+    constexpr int lanes = 16 * G2, per = 64 / lanes;
+    const int w = threadIdx.x / lanes, idx = blockIdx.x * per + w;
+    if (idx >= a.m) return;
+    eval_monomial_team_c<L, G2>(a, a.order[idx], threadIdx.x - w * lanes, lds + (size_t)w * team_doubles_c<L, G2>());
+  }
+}
+
+template <int L, int G2>
+static void launch_team_complex(const EvalArgs &a, hipStream_t st) {
+  constexpr int lanes = 16 * G2, per = lanes < 64 ? 64 / lanes : 1;
+  const size_t lds = per * team_doubles_c<L, G2>() * sizeof(double);
+  static const bool large = [] {
+    (void)hipFuncSetAttribute((const void *)evaldiff_team_complex_kernel<L, G2>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+    (void)hipGetLastError();  // an attribute the runtime refuses must not be reported by the launch
+    return true;
+  }();
+  (void)large;
+  hipLaunchKernelGGL((evaldiff_team_complex_kernel<L, G2>), dim3((a.m + per - 1) / per), dim3(per * lanes), lds, st, a);
+}
+
 // Workers of 2G lanes; WIDE: one worker per workgroup of 2G = 128 threads,
 // else workgroups of one wavefront holding 64 / (2G) workers.
 template <int L, bool WIDE>
@@ -280,6 +498,18 @@ static hipError_t launch_evaldiff_complex_T(const EvalArgs &a, hipStream_t st) {
   const int G = worker_lanes(a.Dc), G2L = 2 * G;
   const size_t per = 6 * (size_t)L * (a.Dc + 1) * sizeof(double);
   if (a.m <= 0) return hipSuccess;
+  if constexpr (L < 8) {  // (octo doubles: 16 wavefronts of a monomial have no room for their registers)
+    switch (pair_lanes(a.Dc)) {
+      case 1: launch_team_complex<L, 1>(a, st); break;
+      case 2: launch_team_complex<L, 2>(a, st); break;
+      case 4: launch_team_complex<L, 4>(a, st); break;
+      case 8: launch_team_complex<L, 8>(a, st); break;
+      case 16: launch_team_complex<L, 16>(a, st); break;
+      case 32: launch_team_complex<L, 32>(a, st); break;
+      case 64: launch_team_complex<L, 64>(a, st); break;
+    }
+    return hipGetLastError();
+  }
   if (G2L > 64) {
     hipLaunchKernelGGL((evaldiff_complex_kernel<L, true>), dim3(a.m), dim3(G2L), per, st, a);
   } else {

@@ -387,19 +387,10 @@ __device__ __forceinline__ void team_sync() {
   else wave_sync();
 }
 
-// The level sums of the lane's terms of U V: part2 of output o2, part1 of o1.
-template <int L, int G2>
-__device__ __forceinline__ void team_conv(const double *U, const double *V, const TeamLane<G2> &q, double (&part1)[L],
-                                          double (&part2)[L]) {
-  constexpr int Dp = 2 * G2 + 1;
-  double acc[L], parked[L];
-  md::zero<L>(acc);
-  md::zero<L>(parked);
-  const int H = ((q.D + 2) / 2 + 1) / 2;  // terms of quarter 0; the others have as many or one less
-  const bool ahead = q.t0 <= q.o2;
-  const int i0 = ahead ? q.t0 : q.t0 - q.o2 - 1;
-  const double *pu = U + i0, *pv = V + ((ahead ? q.o2 : q.o1) - i0), *const pv1 = V + q.o1;
-  auto term = [&] {
+// acc += u v for the entries u and v of two series in LDS.
+template <int L, int G2> struct TeamTerm {
+  __device__ __forceinline__ void operator()(const double *pu, const double *pv, double (&acc)[L]) const {
+    constexpr int Dp = 2 * G2 + 1;
     double u[L], v[L];
 #pragma unroll
     for (int l = 0; l < L; ++l) {
@@ -407,7 +398,21 @@ __device__ __forceinline__ void team_conv(const double *U, const double *V, cons
       v[l] = pv[l * Dp];
     }
     MD<L>::fma_lazy(acc, u, v);
-  };
+  }
+};
+
+// The level sums of the lane's terms of U V: part2 of output o2, part1 of o1.
+template <int L, int G2, class Term>
+__device__ __forceinline__ void team_conv(const double *U, const double *V, const TeamLane<G2> &q, const Term &add,
+                                          double (&part1)[L], double (&part2)[L]) {
+  double acc[L], parked[L];
+  md::zero<L>(acc);
+  md::zero<L>(parked);
+  const int H = ((q.D + 2) / 2 + 1) / 2;  // terms of quarter 0; the others have as many or one less
+  const bool ahead = q.t0 <= q.o2;
+  const int i0 = ahead ? q.t0 : q.t0 - q.o2 - 1;
+  const double *pu = U + i0, *pv = V + ((ahead ? q.o2 : q.o1) - i0), *const pv1 = V + q.o1;
+  auto term = [&] { add(pu, pv, acc); };
   const int park = q.o2 - q.t0;  // o2's last term
   auto advance = [&](int tt) {
     const bool change = tt == park;
@@ -444,11 +449,60 @@ __device__ __forceinline__ void team_conv(const double *U, const double *V, cons
   }
 }
 
+// The sums of the team's parts, rounded, in the lanes that finish them; every
+// read of the product's operands is done when it returns.  X: see
+// team_exchange.
+template <int L, int G2, bool WIDE>
+__device__ __forceinline__ void team_sum(const TeamLane<G2> &q, double *X, const double (&part1)[L],
+                                         const double (&part2)[L], double (&r)[L]) {
+  double mine[L], send[L], o[L];
+  // quarters 0, 1, 2 go on with o2, quarter 3 with o1
+#pragma unroll
+  for (int l = 0; l < L; ++l) {
+    mine[l] = q.quarter == 3 ? part1[l] : part2[l];
+    send[l] = q.quarter == 2 ? part1[l] : part2[l];
+  }
+  if constexpr (G2 <= 32) {
+#pragma unroll
+    for (int l = 0; l < L; ++l) o[l] = __shfl_xor(send[l], G2, 64);
+  } else {
+    if (q.quarter > 0) {
+#pragma unroll
+      for (int l = 0; l < L; ++l) X[(q.quarter * L + l) * G2 + q.p] = send[l];
+    }
+    team_sync<WIDE>();
+#pragma unroll
+    for (int l = 0; l < L; ++l) o[l] = q.quarter == 1 ? 0.0 : X[((q.quarter ^ 1) * L + l) * G2 + q.p];
+  }
+  MD<L>::add_lazy(mine, o);
+  if constexpr (G2 <= 16) {
+#pragma unroll
+    for (int l = 0; l < L; ++l) o[l] = __shfl_xor(mine[l], 2 * G2, 64);
+    team_sync<WIDE>();
+  } else {
+    if (q.quarter == 2) {
+#pragma unroll
+      for (int l = 0; l < L; ++l) X[l * G2 + q.p] = mine[l];
+    }
+    team_sync<WIDE>();
+#pragma unroll
+    for (int l = 0; l < L; ++l) o[l] = X[l * G2 + q.p];
+  }
+  if (q.quarter == 0) MD<L>::add_lazy(mine, o);
+  MD<L>::renorm(mine, r);
+}
+
+// Doubles of a team's exchange of partial sums.
+template <int L, int G2>
+constexpr int team_exchange() {
+  return (G2 > 32 ? 4 : G2 > 16 ? 1 : 0) * G2 * L;
+}
+
 // LDS of one monomial: U and V of both teams, then per team the exchange of
 // partial sums.
 template <int L, int G2>
 constexpr size_t team_doubles() {
-  return (size_t)(4 * (2 * G2 + 1) + 2 * (G2 > 32 ? 4 : G2 > 16 ? 1 : 0) * G2) * L;
+  return (size_t)4 * (2 * G2 + 1) * L + 2 * team_exchange<L, G2>();
 }
 
 template <int L, int G2>
@@ -464,7 +518,7 @@ __device__ void eval_monomial_team(const EvalArgs &a, int mono, int tid, double 
   const int s = owner ? q.own : 0;
   double *UA = lds;
   double *Uown = lds + team * 2 * L * Dp, *V = Uown + L * Dp;
-  double *X = lds + 4 * L * Dp + team * (G2 > 32 ? 4 : 1) * G2 * L;
+  double *X = lds + 4 * L * Dp + team * team_exchange<L, G2>();
   for (int r = tl; r < 4 * L; r += TL) lds[r * Dp + Dc] = 0.0;
   int e0 = a.mon_ptr[mono], e1 = a.mon_ptr[mono + 1];
   if constexpr (ALONE) {
@@ -563,49 +617,14 @@ __device__ void eval_monomial_team(const EvalArgs &a, int mono, int tid, double 
     }
     if (!scalar) {  // r = U V, this lane's coefficient; U and V are free afterwards
       team_sync<WIDE>();
-      double mine[L], send[L];
+      double part1[L], part2[L];
       if (run) {
-        team_conv<L, G2>(j < 1 ? Uown : UA, V, q, send, mine);
-        // quarters 0, 1, 2 go on with o2, quarter 3 with o1
-#pragma unroll
-        for (int l = 0; l < L; ++l) {
-          const double p1 = send[l], p2 = mine[l];
-          mine[l] = q.quarter == 3 ? p1 : p2;
-          send[l] = q.quarter == 2 ? p1 : p2;
-        }
+        team_conv<L, G2>(j < 1 ? Uown : UA, V, q, TeamTerm<L, G2>(), part1, part2);
       } else {
-        md::zero<L>(mine);
-        md::zero<L>(send);
+        md::zero<L>(part1);
+        md::zero<L>(part2);
       }
-      double o[L];
-      if constexpr (G2 <= 32) {
-#pragma unroll
-        for (int l = 0; l < L; ++l) o[l] = __shfl_xor(send[l], G2, 64);
-      } else {
-        if (q.quarter > 0) {
-#pragma unroll
-          for (int l = 0; l < L; ++l) X[(q.quarter * L + l) * G2 + q.p] = send[l];
-        }
-        team_sync<WIDE>();
-#pragma unroll
-        for (int l = 0; l < L; ++l) o[l] = q.quarter == 1 ? 0.0 : X[((q.quarter ^ 1) * L + l) * G2 + q.p];
-      }
-      MD<L>::add_lazy(mine, o);
-      if constexpr (G2 <= 16) {
-#pragma unroll
-        for (int l = 0; l < L; ++l) o[l] = __shfl_xor(mine[l], 2 * G2, 64);
-        team_sync<WIDE>();
-      } else {
-        if (q.quarter == 2) {
-#pragma unroll
-          for (int l = 0; l < L; ++l) X[l * G2 + q.p] = mine[l];
-        }
-        team_sync<WIDE>();
-#pragma unroll
-        for (int l = 0; l < L; ++l) o[l] = X[l * G2 + q.p];
-      }
-      if (q.quarter == 0) MD<L>::add_lazy(mine, o);
-      MD<L>::renorm(mine, r);
+      team_sum<L, G2, WIDE>(q, X, part1, part2, r);
     }
     if (isA) {
       if (run) md::copy<L>(r, f);

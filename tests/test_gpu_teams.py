@@ -31,3 +31,17 @@ def test_eval_diff(L, D):
     ob, oA, scale = oracle.eval_diff(s, s.cff, cst, x)
     assert scaled_err(host(b), ob, scale) <= TOL[L]
     assert matrix_series_err(host(A), oA) <= TOL[L]
+
+
+@pytest.mark.parametrize("L,D", [(L, D) for L in (2, 4) for D in (1, 2, 3, 5, 8, 9, 16, 17, 32, 33, 65, 128)])
+def test_complex_eval_diff(L, D):
+    import paper_2301_12659_amd as mdn
+
+    from test_gpu_complex import cerr
+
+    s = mdinputs.tiny(L, N, D - 1, mons=4, kmin=1, kmax=4, exps=(1, 2), seed=D)
+    cff, cst, x = mdinputs.complex_random(s, 60 + D)
+    b, A = mdn.ComplexNewton(s, cff, cst, x).eval_diff()
+    ref = oracle.complex_step(s, cff, cst, x, step=False)
+    assert cerr(host(b), ref["b"]) <= TOL[L]
+    assert cerr(host(A), np.moveaxis(ref["A"], 2, -1)) <= TOL[L]
