@@ -232,7 +232,7 @@ int series_solve_impl(int L, int n, int D, double *qr, double *tau, const double
   }
   {
     Timed t(MD_CLASS_QHB_BS, st);
-    if ((e = mdk::launch_form_m(L, n, qr, tau, invd, M, status, st, need)) != hipSuccess) return hip_fail(e, "form M");
+    if ((e = mdk::launch_form_m(L, n, qr, tau, invd, M, status, st, need, N)) != hipSuccess) return hip_fail(e, "form M");
   }
   {
     Timed t(MD_CLASS_UPDATES, st);
@@ -1076,7 +1076,7 @@ int md_adjoint_solve(int prec, int n, int d, const double *qr, const double *tau
          *lamT = take((size_t)L * nD);
   int *sync = reinterpret_cast<int *>(take(mdk::stages_sync_ints(D) / 2 + 1));
   hipError_t e;
-  if ((e = mdk::launch_form_m(L, n, qr, tau, invd, M, dev_status, st)) != hipSuccess) return hip_fail(e, "form M");
+  if ((e = mdk::launch_form_m(L, n, qr, tau, invd, M, dev_status, st, nullptr, Nt)) != hipSuccess) return hip_fail(e, "form M");
   if ((e = mdk::launch_transpose(L, M, Mt, n, n, nn, nn, st)) != hipSuccess) return hip_fail(e, "M^T");
   if ((e = mdk::launch_transpose(L, A, At, nn, D, nn * D, nn * D, st)) != hipSuccess) return hip_fail(e, "A^T");
   if ((e = mdk::launch_transpose(L * D, At, AtT, n, n, nn, nn, st)) != hipSuccess) return hip_fail(e, "A_k^T");

@@ -101,8 +101,9 @@ hipError_t launch_qr_lds(int L, int n, double *a, double *tau, double *qt, int32
 hipError_t launch_m_from_qt(int L, int n, const double *qr, const double *qt, double *invd, double *M,
                             int32_t *status, hipStream_t st, double *rs = nullptr, int *done = nullptr,
                             const int *need = nullptr);
+// (qrT, nullable: scratch [L][n][n])
 hipError_t launch_form_m(int L, int n, const double *qr, const double *tau, double *invd, double *M, int32_t *status,
-                         hipStream_t st, const int *need = nullptr);
+                         hipStream_t st, const int *need = nullptr, double *qrT = nullptr);
 hipError_t launch_extract(int L, int n, int D, int k, const double *A, double *out, hipStream_t st);
 hipError_t launch_transpose(int L, const double *in, double *out, size_t rows, int cols, size_t in_ls,
                             size_t out_ls, hipStream_t st);

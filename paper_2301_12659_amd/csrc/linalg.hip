@@ -594,11 +594,12 @@ __global__ void zero_i32_kernel(int *p, int count) {
 template <int L>
 __global__ void invdiag_kernel(int n, const double *qr, double *invd, int32_t *status, const int *need) {
   if (need && *need == 0) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;  // (workgroups of one wavefront)
   const size_t nn = (size_t)n * n;
   double rmax = 0.0;
-  for (int j = 0; j < n; ++j) rmax = fmax(rmax, fabs(qr[(size_t)j * n + j]));
+  for (int j = threadIdx.x; j < n; j += 64) rmax = fmax(rmax, fabs(qr[(size_t)j * n + j]));
+  for (int off = 32; off > 0; off >>= 1) rmax = fmax(rmax, __shfl_xor(rmax, off, 64));
+  if (i >= n) return;
   double r[L], one[L], q[L];
   ld<L>(qr, nn, (size_t)i * n + i, r);
   md::zero<L>(one);
@@ -703,6 +704,96 @@ __global__ void __launch_bounds__(64, 1) form_m_kernel(int n, const double *qr, 
   }
 }
 
+// Lane i's double in every lane (i uniform over the wavefront).
+__device__ __forceinline__ double read_lane(double x, int i) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_readlane((int)b, i);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// The same with y in registers (n <= 64 RW: row i in lane i mod 64) and the
+// factors transposed (qrT[j][i], so that a column is read by whole cache
+// lines), the next column on its way while the current one is used.  A
+// wavefront's issue rate is the bound, about 45 FP64 instructions a reflector
+// and 6 per lane level of its sum in double doubles.  Measured (double double,
+// n = 150): 143 us, where form_m_kernel, each step waiting for a strided
+// column, takes 278 (quad double, n = 32: 66 against 117).
+template <int L, int RW>
+__global__ void __launch_bounds__(64, 1) form_m_reg_kernel(int n, const double *qrT, const double *tau,
+                                                        const double *invd, double *M) {
+  const int c = blockIdx.x, lane = threadIdx.x;
+  const size_t nn = (size_t)n * n;
+  double y[RW][L], next[RW][L], sc[L];
+  // rows of column j from row `from` on, zero elsewhere
+  auto fetch = [&](int j, int from, int to) {
+#pragma unroll
+    for (int s = 0; s < RW; ++s) {
+      const int i = lane + 64 * s;
+      md::zero<L>(next[s]);
+      if (i >= from && i < to) ld<L>(qrT, nn, (size_t)j * n + i, next[s]);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < RW; ++s) {
+    md::zero<L>(y[s]);
+    if (lane + 64 * s == c) y[s][0] = 1.0;
+  }
+  fetch(0, 1, n);
+  ld<L>(tau, n, 0, sc);
+  for (int r = 0; r < n; ++r) {
+    double v[RW][L], tr[L], dot[L], d[L], w[L];
+    md::copy<L>(sc, tr);
+#pragma unroll
+    for (int s = 0; s < RW; ++s) {
+      md::copy<L>(next[s], v[s]);
+      if (lane + 64 * s == r) v[s][0] = 1.0;
+    }
+    if (r + 1 < n) {
+      fetch(r + 1, r + 2, n);
+      ld<L>(tau, n, r + 1, sc);
+    }
+    md::zero<L>(dot);
+#pragma unroll
+    for (int s = 0; s < RW; ++s)
+      if (64 * s + 64 > r) MD<L>::fma_lazy(dot, v[s], y[s]);
+    team_sum_lazy<L>(dot, 64);
+    MD<L>::renorm(dot, d);
+    MD<L>::mul(d, tr, w);
+#pragma unroll
+    for (int s = 0; s < RW; ++s)
+      if (64 * s + 64 > r) MD<L>::fms(y[s], v[s], w);
+  }
+  fetch(n - 1, 0, n - 1);
+  ld<L>(invd, n, n - 1, sc);
+  for (int i = n - 1; i >= 0; --i) {
+    double rp[RW][L], di[L], yi[L], z[L];
+    md::copy<L>(sc, di);
+#pragma unroll
+    for (int s = 0; s < RW; ++s) md::copy<L>(next[s], rp[s]);
+    if (i > 0) {
+      fetch(i - 1, 0, i - 1);
+      ld<L>(invd, n, i - 1, sc);
+    }
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      double e = y[0][l];
+#pragma unroll
+      for (int s = 1; s < RW; ++s) e = (i >> 6) == s ? y[s][l] : e;
+      yi[l] = read_lane(e, i & 63);
+    }
+    MD<L>::mul(yi, di, z);
+#pragma unroll
+    for (int s = 0; s < RW; ++s) {
+      if (64 * s < i) MD<L>::fms(y[s], rp[s], z);
+      if (lane + 64 * s == i) md::copy<L>(z, y[s]);
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < RW; ++s)
+    if (lane + 64 * s < n) st<L>(M, nn, (size_t)(lane + 64 * s) * n + c, y[s]);
+}
+
 // Column c of M = R^{-1} Q^T from an explicit Q^T (rows of the QR kernel's
 // augmented part): one wavefront per column.
 template <int L>
@@ -726,14 +817,6 @@ __global__ void __launch_bounds__(64, 1) m_from_qt_kernel(int n, const double *q
     for (int l = 0; l < L; ++l) zi[l] = y[l * n + i];
     st<L>(M, nn, (size_t)i * n + c, zi);
   }
-}
-
-// Lane i's double in every lane (i uniform over the wavefront).
-__device__ __forceinline__ double read_lane(double x, int i) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readlane((int)b, i);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), i);
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
 // The rows of R scaled by their diagonal entries, for the back substitution
@@ -1712,7 +1795,26 @@ hipError_t launch_m_from_qt(int L, int n, const double *qr, const double *qt, do
 }
 
 hipError_t launch_form_m(int L, int n, const double *qr, const double *tau, double *invd, double *M, int32_t *status,
-                         hipStream_t st, const int *need) {
+                         hipStream_t st, const int *need, double *qrT) {
+  // up to 192 rows (double and quad doubles; octo doubles 128) a wavefront
+  // holds a column of M in its registers
+  if (!need && qrT && n <= (L == 8 ? 128 : 192)) {
+    hipError_t e = launch_transpose(L, qr, qrT, n, n, (size_t)n * n, (size_t)n * n, st);
+    if (e != hipSuccess) return e;
+    MD_DISPATCH(L, {
+      hipLaunchKernelGGL(invdiag_kernel<LL>, dim3((n + 63) / 64), dim3(64), 0, st, n, qr, invd, status, need);
+      if (n <= 64)
+        hipLaunchKernelGGL((form_m_reg_kernel<LL, 1>), dim3(n), dim3(64), 0, st, n, (const double *)qrT, tau,
+                           (const double *)invd, M);
+      else if (n <= 128)
+        hipLaunchKernelGGL((form_m_reg_kernel<LL, 2>), dim3(n), dim3(64), 0, st, n, (const double *)qrT, tau,
+                           (const double *)invd, M);
+      else if constexpr (LL < 8)
+        hipLaunchKernelGGL((form_m_reg_kernel<LL, 3>), dim3(n), dim3(64), 0, st, n, (const double *)qrT, tau,
+                           (const double *)invd, M);
+    });
+    return hipGetLastError();
+  }
   MD_DISPATCH(L, {
     static bool attr = false;
     if (!attr) {

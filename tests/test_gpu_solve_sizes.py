@@ -1,0 +1,43 @@
+"""QR, M = R^{-1} Q^T and the staged solve of A(t) dx(t) = b(t) at the edges of
+their kernels' sizes: the residual of the solution."""
+import numpy as np
+import pytest
+
+import mdinputs
+from gpu_helpers import TOL, dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L,n", [(L, n) for L in (2, 4) for n in (1, 2, 63, 64, 65, 77, 127, 128, 129, 191, 192, 193)] +
+                         [(8, 5), (8, 64), (8, 65), (8, 129)])
+@pytest.mark.parametrize("D", [1, 2, 11])
+def test_residual_of_the_solution(L, n, D):
+    import torch
+
+    import paper_2301_12659_amd as mdn
+
+    rng = np.random.default_rng([L, n, D])
+    A = mdinputs.random_md(rng, L, (n, n, D), -1.0, 1.0)
+    i = np.arange(n)
+    A[0, i, i, 0] += 2.0 * n  # the sums of a row's other terms stay below it
+    A[:, :, :, 1:] *= 0.25
+    b = mdinputs.random_md(rng, L, (n, D), -1.0, 1.0)
+    tA, tb = dev(np.ascontiguousarray(A)), dev(np.ascontiguousarray(b))
+    a0 = tA[..., 0].clone(memory_format=torch.contiguous_format)  # (factorized in place)
+    tau = torch.zeros((L, n), dtype=torch.float64, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    mdn.qr(L, n, a0, tau, status)
+    dx = tb.clone()
+    ws = mdn.workspace(mdn.solve_workspace_bytes(L, n, D - 1))
+    mdn.series_solve(L, n, D - 1, a0, tau, tA, dx, ws, status)
+    r = torch.empty_like(tb)
+    mdn.linear_residual(L, n, D - 1, tA, tb, dx, r)
+    torch.cuda.synchronize()
+    assert int(status) == 0
+    x = np.abs(host(dx)[0])
+    size = np.abs(b[0])
+    for k in range(D):
+        for j in range(k + 1):
+            size[:, k] += np.abs(A[0, :, :, j]) @ x[:, k - j]
+    assert float((np.abs(host(r)[0]) / size).max()) <= TOL[L]
