@@ -548,7 +548,7 @@ static int newton_step_impl(const md_plan *p, int Ls, int lo, int hi, bool keep_
       Timed t(MD_CLASS_QR, st);
       eval_args(p, cff, x, ws, 1, a);
       if (pre0) a.reset_status = dev_status;
-      e = pre0 ? mdk::launch_evaldiff0(Ls, a, st) : mdk::launch_evaldiff(Ls, a, p->maxexp, at(ws, w.pw), st);
+      e = pre0 ? mdk::launch_evaldiff0(Ls, a, st) : mdk::launch_evaldiff0_scan(Ls, a, p->maxk, st);
       a.reset_status = nullptr;
       if (e != hipSuccess) return hip_fail(e, "A_0 pre-pass");
       // (its launch also prepares the QR's hand-over memory)

@@ -40,6 +40,8 @@ hipError_t launch_evaldiff_digits(int L, const EvalArgs &a, hipStream_t st);
 // evaldiff0_max_support(L) variables (none for octo doubles).
 hipError_t launch_evaldiff0(int L, const EvalArgs &a, hipStream_t st);
 int evaldiff0_max_support(int L);
+// The same for supports of any size (the largest: maxk).
+hipError_t launch_evaldiff0_scan(int L, const EvalArgs &a, int maxk, hipStream_t st);
 // A coefficient-major copy written by an assembly kernel beside its
 // series-major output: p[l][s - lo][q] for lo <= s < lo + W and limbs l < L
 // (a window of the coefficients, its leading limbs), q the row (b) or the
