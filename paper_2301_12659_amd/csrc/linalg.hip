@@ -1124,6 +1124,99 @@ __global__ void __launch_bounds__(256) gemm_next_x0_kernel(int n, int D, const d
   }
 }
 
+// The whole staged solve of a small system (n <= T) in one workgroup, everything
+// in LDS: the first T T threads form dx_k = M r_k - N dx_{k-1}, T lanes a row,
+// with M and N in registers, while the others push the terms A_{m-k+1} dx_{k-1}
+// of the later right-hand sides r_m, m > k, four lanes an entry.  A stage is one
+// barrier instead of a hand-over between workgroups through memory (double
+// double, n = 8, 16 stages: 20.5 us in stages_persistent_kernel).  A in
+// LDS as [v][k][i]: neighbouring entries in neighbouring banks.  The sums of a
+// row are those of next_x0_block, which has 64 lanes for them.
+template <int L, int T>
+__global__ void __launch_bounds__(512) stages_small_kernel(int n, int D, const double *M, const double *N,
+                                                        const double *At, const double *rT, double *dxT) {
+  constexpr int CH = T * T, U = 4;
+  extern __shared__ double lds[];
+  const int tid = threadIdx.x, nn = n * n, nD = n * D, nnD = nn * D;
+  double *As = lds, *rs = lds + (size_t)L * nnD, *xs = rs + (size_t)L * nD;  // xs [2][L][n]
+  const int i = tid / T, tl = tid % T;
+  const bool term = tid < CH && i < n && tl < n;
+  double m[L], nv[L];
+  md::zero<L>(m);
+  md::zero<L>(nv);
+  if (term) {
+    ld<L>(M, nn, (size_t)i * n + tl, m);
+    if (D > 1) ld<L>(N, nn, (size_t)i * n + tl, nv);
+    md::neg<L>(nv, nv);
+  }
+  for (int e = tid; e < nnD; e += 512) {
+    const int k = e / nn, ij = e - k * nn, row = ij / n, v = ij - row * n;
+#pragma unroll
+    for (int l = 0; l < L; ++l) As[l * nnD + v * nD + k * n + row] = At[(size_t)l * nnD + e];
+  }
+  for (int e = tid; e < L * nD; e += 512) rs[e] = rT[e];
+  __syncthreads();
+  for (int k = 0; k < D; ++k) {
+    const double *xp = xs + ((k + 1) & 1) * L * n;  // dx_{k-1}
+    if (tid < CH) {
+      double acc[L], r[L], a[L];
+      md::zero<L>(acc);
+      const int v = min(tl, n - 1);
+#pragma unroll
+      for (int l = 0; l < L; ++l) a[l] = rs[l * nD + k * n + v];
+      if (term) MD<L>::fma_lazy(acc, m, a);
+      if (k > 0) {
+#pragma unroll
+        for (int l = 0; l < L; ++l) a[l] = xp[l * n + v];
+        if (term) MD<L>::fma_lazy(acc, nv, a);
+      }
+      team_sum_lazy<L>(acc, T);
+      MD<L>::renorm(acc, r);
+      if (tl == 0 && i < n) {
+        double *x = xs + (k & 1) * L * n;
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+          x[l * n + i] = r[l];
+          dxT[(size_t)l * nD + k * n + i] = r[l];
+        }
+      }
+    } else if (k > 0) {
+      const int ul = tid % U;
+      for (int e0 = (k + 1) * n; e0 < nD; e0 += (512 - CH) / U) {  // entries (m, i) of the right-hand sides
+        const int e = e0 + (tid - CH) / U;
+        double acc[L], s[L], r[L], d[L];
+        md::zero<L>(acc);
+        if (e < nD) {
+          const double *a0 = As + e - (k - 1) * n;
+#pragma unroll
+          for (int c = 0; c < T / U; ++c) {
+            const int v = ul + U * c;
+            if (v < n) {
+              double a[L], x[L];
+#pragma unroll
+              for (int l = 0; l < L; ++l) {
+                a[l] = a0[l * nnD + v * nD];
+                x[l] = xp[l * n + v];
+              }
+              MD<L>::fma_lazy(acc, a, x);
+            }
+          }
+        }
+        team_sum_lazy<L>(acc, U);
+        MD<L>::renorm(acc, s);
+        if (e < nD && ul == 0) {
+#pragma unroll
+          for (int l = 0; l < L; ++l) r[l] = rs[l * nD + e];
+          MD<L>::sub(r, s, d);
+#pragma unroll
+          for (int l = 0; l < L; ++l) rs[l * nD + e] = d[l];
+        }
+      }
+    }
+    __syncthreads();
+  }
+}
+
 // Counters of the persistent staged solve: the updaters' counters one per
 // 256 bytes, the solvers' flags packed into the second block of 256 bytes.
 constexpr int SYNC_STRIDE = 64;
@@ -1887,17 +1980,26 @@ bool stages_persistent(int L, int n, int D) {
   return ((L == 2 && n <= 192) || (L == 4 && n <= 128)) && D >= 1 && stages_grid(n, D).fits;
 }
 
+// One workgroup's staged solve (stages_small_kernel): up to two limbs, A within
+// 60 KB of LDS.  Double double, n = 8, 16 stages: 11 us, 20.5 in the persistent
+// kernel.  Four limbs: one workgroup's multiply-adds take longer than the
+// hand-overs that they save.
+static size_t stages_small_doubles(int L, int n, int D) { return (size_t)L * n * ((size_t)n * D + D + 2); }
+static bool stages_small(int L, int n, int D) {
+  return L <= 2 && n <= 16 && stages_small_doubles(L, n, D) * sizeof(double) <= 60 * 1024;
+}
+
 int stages_sync_ints(int D) { return (D + 2 + 64) * SYNC_STRIDE; }
 
 int stages_products(int L, int n, int D) {
-  return stages_persistent(L, n, D) ? std::min(STAGE_PRODUCTS, D - 1) : std::min(1, D - 1);
+  return stages_persistent(L, n, D) && !stages_small(L, n, D) ? std::min(STAGE_PRODUCTS, D - 1) : std::min(1, D - 1);
 }
 
 // The counters of the persistent staged solve cleared ahead of it (a caller
 // may issue this before it waits for the factorization, off the critical
 // path, and then launch_stages with sync_ready).
 hipError_t launch_stages_sync(int L, int n, int D, int *sync, double *dxT, hipStream_t st) {
-  if (stages_persistent(L, n, D)) {
+  if (stages_persistent(L, n, D) && !stages_small(L, n, D)) {
     const size_t cnt = std::max((size_t)stages_sync_ints(D), (size_t)L * n * D);
     hipLaunchKernelGGL(stages_prep_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, sync,
                        stages_sync_ints(D), dxT, (size_t)L * n * D);
@@ -1907,6 +2009,17 @@ hipError_t launch_stages_sync(int L, int n, int D, int *sync, double *dxT, hipSt
 
 hipError_t launch_stages(int L, int n, int D, const double *M, const double *NP, const double *At, double *rT,
                          double *dxT, int *sync, int32_t *status, hipStream_t st, bool sync_ready) {
+  if (stages_small(L, n, D)) {
+    const size_t lds = stages_small_doubles(L, n, D) * sizeof(double);
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(1), dim3(512), lds, st, n, D, M, NP, At, (const double *)rT, dxT);
+    };
+    if (L == 2 && n <= 8) run(stages_small_kernel<2, 8>);
+    else if (L == 2) run(stages_small_kernel<2, 16>);
+    else if (n <= 8) run(stages_small_kernel<1, 8>);
+    else run(stages_small_kernel<1, 16>);
+    return hipGetLastError();
+  }
   if (stages_persistent(L, n, D)) {
     const StagesGrid g = stages_grid(n, D);
     const int G = g.solvers + g.groups * g.row_blocks;

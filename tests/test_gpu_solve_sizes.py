@@ -9,9 +9,9 @@ from gpu_helpers import TOL, dev, host
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("L,n", [(L, n) for L in (2, 4) for n in (1, 2, 63, 64, 65, 77, 127, 128, 129, 191, 192, 193)] +
-                         [(8, 5), (8, 64), (8, 65), (8, 129)])
-@pytest.mark.parametrize("D", [1, 2, 11])
+@pytest.mark.parametrize("L,n", [(L, n) for L in (2, 4) for n in (1, 2, 8, 9, 16, 17, 63, 64, 65, 77, 127, 128, 129, 191, 192, 193)] +
+                         [(1, 7), (1, 16), (8, 5), (8, 64), (8, 65), (8, 129)])
+@pytest.mark.parametrize("D", [1, 2, 11, 27])
 def test_residual_of_the_solution(L, n, D):
     import torch
 
