@@ -28,7 +28,8 @@ FLAGS = [
     "-Wno-unused-command-line-argument",
 ]
 
-SOURCES = ["evaldiff.hip", "evaldigits.hip", "assemble.hip", "linalg.hip", "inverse.hip", "residual.hip", "complex.hip", "api.hip", "batch.hip"]
+SOURCES = ["evaldiff.hip", "evaldigits.hip", "assemble.hip", "linalg.hip", "inverse.hip", "prepass.hip", "residual.hip",
+           "complex.hip", "api.hip", "batch.hip"]
 
 
 def _compile(src: str) -> str:

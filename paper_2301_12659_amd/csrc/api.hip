@@ -540,7 +540,16 @@ static int newton_step_impl(const md_plan *p, int Ls, int lo, int hi, bool keep_
   double *invd = at(ws, w.invd), *M = at(ws, w.M), *N = at(ws, w.N), *r = at(ws, w.r), *dx = at(ws, w.dx);
   double *tsz = scale ? at(ws, w.tsz) : nullptr;
   mdk::EvalArgs a;
-  if (!keep_m) {
+  const bool small = !keep_m && mdk::prepass_small(Ls, n, p->m, p->maxk);
+  if (small) {
+    // 1., 2. in one launch on the caller's stream
+    Timed t(MD_CLASS_QR, st);
+    eval_args(p, cff, x, ws, 1, a);
+    a.reset_status = dev_status;
+    e = mdk::launch_prepass_small(Ls, a, p->d_asm_ptr, p->d_asm_ent, qr, qt, invd, M, dev_status, nullptr, st);
+    a.reset_status = nullptr;
+    if (e != hipSuccess) return hip_fail(e, "M");
+  } else if (!keep_m) {
     // 1. pre-pass: coefficient 0 of every derivative product gives A_0 (the
     //    same products as the full evaluation, rounded in another order: the
     //    solve uses this A_0 throughout, for M and for the stages)
@@ -626,7 +635,7 @@ static int newton_step_impl(const md_plan *p, int Ls, int lo, int hi, bool keep_
     }
   }
   // 4. join, N = M A_1 (and P = M A_2, Q = M A_3), the staged solve of the window
-  if (!keep_m && (e = hipStreamWaitEvent(st, p->join, 0)) != hipSuccess) return hip_fail(e, "join wait");
+  if (!keep_m && !small && (e = hipStreamWaitEvent(st, p->join, 0)) != hipSuccess) return hip_fail(e, "join wait");
   if (W > 1) {
     Timed t(MD_CLASS_GEMM, st);
     if ((e = mdk::launch_gemm(Ls, n, M, At + nn, nn * W, N, mdk::stages_products(Ls, n, W), st)) != hipSuccess)
@@ -703,6 +712,7 @@ static int newton_steps_impl(const md_plan *p, int count, const double *cff, con
   // event is recorded after the last factorization only (and after every
   // one where the caller's stream waits for it instead of M's count): an
   // event record on the second stream delays its next launch.
+  const bool small = mdk::prepass_small(L, n, p->m, p->maxk);
   auto factor = [&](int k, int xseq_target, bool last) -> int {
     if (xseq_target == 0) {
       if ((e = hipEventRecord(p->fork, st)) != hipSuccess) return hip_fail(e, "fork");
@@ -719,6 +729,13 @@ static int newton_steps_impl(const md_plan *p, int count, const double *cff, con
         a.wait_status = dev_status;
       }
       // the pre-pass is left out of the class timing: it may wait for xn
+      if (small) {
+        if ((e = mdk::launch_prepass_small(L, a, p->d_asm_ptr, p->d_asm_ent, qrs[k], qts[k], invd, Ms[k], dev_status,
+                                           mcount ? mseq : nullptr, p->aux)) != hipSuccess)
+          return hip_fail(e, "M");
+        if ((last || !mcount) && (e = hipEventRecord(p->join, p->aux)) != hipSuccess) return hip_fail(e, "join");
+        return MD_OK;
+      }
       if ((e = mdk::launch_evaldiff0(L, a, p->aux)) != hipSuccess) return hip_fail(e, "A_0 pre-pass");
       Timed t(MD_CLASS_QR, p->aux);
       // (the A_0 assembly also prepares the QR's hand-over memory)

@@ -42,6 +42,12 @@ hipError_t launch_evaldiff0(int L, const EvalArgs &a, hipStream_t st);
 int evaldiff0_max_support(int L);
 // The same for supports of any size (the largest: maxk).
 hipError_t launch_evaldiff0_scan(int L, const EvalArgs &a, int maxk, hipStream_t st);
+// prepass.hip: the coefficient-0 derivatives, A_0 (a0), its inverse M and the
+// status of a small system in one launch (x0 [L][n][n], invd [L][n]: scratch;
+// done, nullable: raised by n once M is complete).
+bool prepass_small(int L, int n, int m, int maxk);
+hipError_t launch_prepass_small(int L, const EvalArgs &a, const int32_t *asm_ptr, const int32_t *asm_ent, double *a0,
+                                double *x0, double *invd, double *M, int32_t *status, int *done, hipStream_t st);
 // A coefficient-major copy written by an assembly kernel beside its
 // series-major output: p[l][s - lo][q] for lo <= s < lo + W and limbs l < L
 // (a window of the coefficients, its leading limbs), q the row (b) or the

@@ -45,3 +45,22 @@ def test_complex_eval_diff(L, D):
     ref = oracle.complex_step(s, cff, cst, x, step=False)
     assert cerr(host(b), ref["b"]) <= TOL[L]
     assert cerr(host(A), np.moveaxis(ref["A"], 2, -1)) <= TOL[L]
+
+
+@pytest.mark.parametrize("D", [1, 2, 5, 9, 17, 33, 65])
+@pytest.mark.parametrize("exps", [(1,), (1, 2, 3)])
+def test_values_only(D, exps):
+    """Steps whose residual alone has four limbs (the values without the derivatives)."""
+    import torch
+
+    import paper_2301_12659_amd as mdn
+
+    s = mdinputs.tiny(4, 5, D - 1, mons=3, kmin=1, kmax=5, exps=exps, seed=3)
+    cst = oracle.manufacture(s)
+    drv = mdn.Newton(s, cst)
+    for _ in range(12):
+        drv.step(prec_solve=2)
+    torch.cuda.synchronize()
+    assert drv.status_code() == 0
+    err = oracle.absdiff(host(drv.x), s.xstar).max(axis=-1) / np.abs(s.xstar[0]).max(axis=-1)
+    assert float(err.max()) <= TOL[4]
