@@ -671,13 +671,13 @@ def main():
         "config": {"workload": "medium_qd: n=64, d=63 (D=64), quad double, 64 x (32 + 1 boost) monomials, "
                                "2..6 variables, exponents {1,2}, manufactured solution, seed 2",
                    "n": n, "d": sysm.d, "precision": "qd", "monomials": sysm.m, "support_entries": sysm.nnz},
-        "steps_entry_point": "md_newton_steps (each step's QR beside the previous step; iterates identical to "
+        "steps_entry_point": "md_newton_steps (each step's A_0^-1 beside the previous step; iterates identical to "
                              "md_newton_step calls)",
         "single_step_ms": round(ms_single, 4),
         "single_step_per_s": round(1000.0 / ms_single, 3),
         "gflops_step": round(total_flops / (ms_step * 1e-3) / 1e9, 2),
         "pct_fp64_peak_step": round(100 * total_flops / (ms_step * 1e-3) / (PEAK_FP64_TFLOPS * 1e12), 2),
-        "roofline": {"bound": "alu", "kernel": "evaldiff_pair_kernel<4> (" + dom + ", two wavefronts per monomial)", "achieved": round(achieved, 3), "peak": PEAK_FP64_TFLOPS,
+        "roofline": {"bound": "alu", "kernel": "evaldiff_team_kernel<4, 32> (" + dom + ", two teams of lanes per monomial)", "achieved": round(achieved, 3), "peak": PEAK_FP64_TFLOPS,
                      "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP64_TFLOPS, 4), "traffic": _recorded_traffic(),
                      "flops_per_launch": w[dom]["flops"], "launch_ms": round(dom_ms, 4)},
         "evaldiff_conventions": conventions,

@@ -152,16 +152,17 @@ int md_newton_step(const md_plan *plan, const double *cff, const double *cst, do
                    double *dev_norms, void *ws, size_t ws_bytes, hipStream_t stream);
 
 /* count plain Newton steps, x := x + dx each time, with results identical bit
- * for bit to count calls of md_newton_step.  The QR of A_0 is on the critical
+ * for bit to count calls of md_newton_step.  M = A_0^{-1} is on the critical
  * path of a single step; here it is taken off: A_0 of the next step depends
  * only on coefficient 0 of the next iterate, x_0 + dx_0, and dx_0 = M b_0
  * (the first stage of the staged solve, Section 2) is formed as soon as the
- * current step has its factorization and its b.  The pre-pass, QR and
- * back substitution of step s+1 then run on the plan's second stream beside
- * the staged solve of step s and the evaluation of step s+1 (the QR is
- * still computed for every step; Section 5.3 computes it once per path).
+ * current step has its M and its b.  The pre-pass and M of step s+1 (by
+ * refinement of an inverse in doubles, or by QR and back substitution where
+ * that does not suit A_0) then run on the plan's second stream beside the
+ * staged solve of step s and the evaluation of step s+1 (M is formed for
+ * every step; Section 5.3 factorizes once per path).
  * This applies to plans whose staged solve runs in one persistent launch
- * (double or quad double, n <= 64) with supports of at most 8 variables;
+ * (double double n <= 192, quad double n <= 128) with supports of at most 8 variables;
  * other plans take count ordinary steps.  The factorization of step s+1
  * waits on the device for the launch that forms its x_0 on the caller's
  * stream, and the caller's stream for M of each step (counters in the

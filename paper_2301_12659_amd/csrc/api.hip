@@ -764,8 +764,7 @@ static int newton_steps_impl(const md_plan *p, int count, const double *cff, con
   for (int s = 0; s < count; ++s) {
     const int k = (count - 1 - s) % 2;
     // the evaluation is on the critical path here (the factorization of the
-    // next step has slack): the two-wavefront kernel (0.69 against 0.75 ms
-    // per step); the assembly also writes the coefficient-major A and b,
+    // next step has slack): two teams of lanes per monomial; the assembly also writes the coefficient-major A and b,
     // clears the staged solve's counters and empties its dx slots, and ends
     // only once M of this step is formed: a wait for its columns' count on
     // the device (the factorizations so far: s + 1), else the join event

@@ -48,7 +48,7 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
 // pivot rows, every other column takes one update of rank NB,
 //     a_i := (i a pivot row of the panel ? 0 : a_i) + sum_m W[i][m] a_{p_m}.
 // One workgroup barrier per panel (the panels alternate between two
-// buffers).  Bound by the chain of the panel owners, about 0.2 us per column
+// buffers).  Bound by the chain of the panel owners, 0.6 (n = 64) to 1 us (n = 128) per column
 // (a maximum over the lanes, lane reads, one division), where one column per
 // barrier with the rows spread over the wavefronts took 1.1 us (n = 64).
 template <int RW, int NB, int NW>

@@ -14,9 +14,10 @@
 // which is A_0^{-1} (b_k - sum_{j=1..k} A_j dx_{k-j}) reassociated so that the
 // only work that waits for dx_{k-1} is one matrix-vector product per row; in
 // the same launch every later right-hand side r_m (m > k) receives its term
-// A_{m-k+1} dx_{k-1}.  Every stage is one launch over the whole GPU; for
-// n <= 64 in double and quad double one persistent launch runs all stages
-// with the recurrence reassociated further (stages_persistent_kernel).
+// A_{m-k+1} dx_{k-1}.  Every stage is one launch over the whole GPU; up to 192
+// (double double) or 128 (quad double) rows one persistent launch runs all
+// stages with the recurrence reassociated further (stages_persistent_kernel),
+// and one workgroup those of a small system (stages_small_kernel).
 #include <algorithm>
 
 #include "common.hpp"
