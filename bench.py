@@ -636,8 +636,9 @@ def main():
     latency = {
         "model": "dependent FP64 instructions on the chain x %.1f cycles at %.1f GHz + %.1f us per hand-over"
                  % (work.CYCLES_PER_DEP_INSTR, work.CLOCK_HZ / 1e9, work.HANDOVER_S * 1e6),
-        "qr_and_m": {"bound_ms": round(qr_b["seconds"] * 1e3, 4), "chain_instr_per_column": qr_b["chain_instr_per_column"],
-                     "measured_ms": round(qr_ms, 4), "frac": round(qr_b["seconds"] * 1e3 / qr_ms, 3)},
+        # M is formed by refinement: the bound of the QR that it replaces stands beside it
+        "qr_and_m": {"qr_bound_ms": round(qr_b["seconds"] * 1e3, 4),
+                     "chain_instr_per_column": qr_b["chain_instr_per_column"], "measured_ms": round(qr_ms, 4)},
         "staged_solve": {"bound_ms": round(st_b["seconds"] * 1e3, 4), "chain_instr_per_stage": st_b["chain_instr_per_stage"],
                          "measured_ms": round(st_ms, 4), "frac": round(st_b["seconds"] * 1e3 / st_ms, 3)},
     }

@@ -28,8 +28,8 @@
 // dependent instructions for the level sums.  The next term's digits are
 // loaded into the registers that the current term's rows leave.  Three series
 // instead of four (the common factor beside the backward chain) leave room for
-// two workgroups per CU at order 128 in octo doubles.  Measured (octo double, 128
-// variables, 512 monomials, order 128; evaldiff.hip 43.9 ms): 17.9 ms with
+// two workgroups per CU at order 128 in octo doubles.  Measured (octo double, 8192
+// monomials, order 128; 43.9 ms by level sums): 17.9 ms with
 // the single products formed by one team while the other waits, 13.7 shared.
 #include "digits.hpp"
 #include "evaldiff_dev.hpp"
@@ -467,7 +467,7 @@ __global__ void __launch_bounds__(4 * G2, 2) evaldiff_digits_kernel(EvalArgs a) 
 }
 
 // Orders whose products fill a team of at least 32 lanes; measured in octo
-// doubles at order 47: 537 us by level sums, 279 on digits.  Quad doubles stay with the
+// doubles at order 41: 537 us by level sums, 279 on digits.  Quad doubles stay with the
 // level sums: 112 instructions per term against 78, and the digits' alignment
 // and rounding cost more than that saves (order 64: 243 us against 316).
 bool evaldiff_on_digits(int L, int Dc) { return L == 8 && Dc > 16; }
