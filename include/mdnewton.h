@@ -302,7 +302,7 @@ int md_newton_step_complex(const md_plan *plan, const double *cff, const double 
 
 /* Batches of independent systems ("paths"; the paper tracks many solution
  * paths of a homotopy, Section 1), one Newton step of every path per call,
- * in one persistent launch.  A path p has n_p (1..128) variables and
+ * in launches over all paths.  A path p has n_p (1..128) variables and
  * polynomials, truncation degree d_p (D_p = d_p + 1 <= MD_MAX_COEFFS) and
  * m_p monomials with exponents 1 or 2; precision double or quad double.
  *
