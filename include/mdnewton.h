@@ -322,8 +322,8 @@ int md_newton_step_complex(const md_plan *plan, const double *cff, const double 
  * (prec_solve below the batch's precision: md_newton_step_mixed).
  * dev_status[p] is the path's status (MD_OK, MD_ESINGULAR, MD_ENONFINITE),
  * dev_norms[2p] = max |b| and dev_norms[2p+1] = max |dx| over the path's
- * series (leading limbs).  The workspace (md_batch_workspace_size) holds a
- * queue counter and one slot of intermediates per concurrent workgroup.
+ * series (leading limbs).  The workspace (md_batch_workspace_size) holds the
+ * intermediates of as many of the largest paths as two per compute unit.
  * The call is asynchronous; it captures its launches in a graph on the
  * second call with the same arguments and replays the graph afterwards.
  * Not thread safe per batch.
