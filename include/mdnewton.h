@@ -367,6 +367,13 @@ int md_arith(int prec, int op, int64_t count, const double *a, const double *b, 
 int md_adjoint_workspace_size(int prec, int n, int d, size_t *bytes);
 int md_adjoint_solve(int prec, int n, int d, const double *qr, const double *tau, const double *A, double *g_lambda,
                      void *ws, size_t ws_bytes, hipStream_t stream, int32_t *dev_status);
+/* The same from A_0 ([L][n][n], overwritten) where no factors are at hand:
+ * A_0^{-1} by refinement of an inverse in doubles, or by the factorization
+ * where that does not suit A_0 (tau [L][n] and qr_ws as md_qr: scratch).
+ * dev_status is set to MD_OK first. */
+int md_adjoint_solve_a0(int prec, int n, int d, double *a0, double *tau, void *qr_ws, size_t qr_ws_bytes,
+                        const double *A, double *g_lambda, void *ws, size_t ws_bytes, hipStream_t stream,
+                        int32_t *dev_status);
 
 /* grad_cff [L][m]: dL/dc_m = -sum_k lambda_{i(m),k} [x^{a_m}]_k, the gradient of
  * a loss L(x) at a solution x of p(x; c) = 0 given lambda from

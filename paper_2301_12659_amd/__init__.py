@@ -75,6 +75,8 @@ _lib.md_arith.argtypes = [_i32, _i32, ctypes.c_int64, _vp, _vp, _vp, _vp]
 _lib.md_last_error.restype = ctypes.c_char_p
 _lib.md_adjoint_workspace_size.argtypes = [_i32, _i32, _i32, _szp]
 _lib.md_adjoint_solve.argtypes = [_i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, ctypes.c_size_t, _vp, _vp]
+_lib.md_adjoint_solve_a0.argtypes = [_i32, _i32, _i32, _vp, _vp, _vp, ctypes.c_size_t, _vp, _vp, _vp,
+                                      ctypes.c_size_t, _vp, _vp]
 _lib.md_coef_grad.argtypes = [_vp, _vp, _vp, _vp, _vp, ctypes.c_size_t, _vp]
 _lib.md_timing_enable.argtypes = [_i32]
 _i64p = ctypes.POINTER(ctypes.c_int64)
@@ -460,6 +462,18 @@ def adjoint_solve(prec, n, d, qr_, tau, A, g_lambda, ws, status, stream=None):
     _check(rc, "md_adjoint_solve")
 
 
+def _adjoint_solve_a0(prec, n, d, a0, tau, A, g_lambda, status, stream=None):
+    """md_adjoint_solve_a0: the adjoint solve from A_0 (overwritten), without factors."""
+    L, D = int(prec), int(d) + 1
+    ws = workspace(adjoint_workspace_bytes(L, n, d), a0.device)
+    qr_ws = workspace(qr_workspace_bytes(L, n), a0.device)
+    rc = _lib.md_adjoint_solve_a0(L, int(n), int(d), _ptr(a0, (L, n, n), "a0"), _ptr(tau, (L, n), "tau"),
+                                  _ptr(qr_ws, None, "ws"), qr_ws.numel() * 8, _ptr(A, (L, n, n, D), "A"),
+                                  _ptr(g_lambda, (L, n, D), "g_lambda"), _ptr(ws, None, "ws"), ws.numel() * 8,
+                                  _stream(stream), _ptr(status, (1,), "status"))
+    _check(rc, "md_adjoint_solve_a0")
+
+
 def coef_grad(plan: Plan, x, lam, grad, ws, stream=None):
     L, n, D, m = plan.prec, plan.n, plan.D, plan.m
     rc = _lib.md_coef_grad(plan._h, _ptr(x, (L, n, D), "x"), _ptr(lam, (L, n, D), "lambda"),
@@ -625,9 +639,8 @@ def _torch_fns():
             a0 = A[..., 0].contiguous()
             tau = torch.zeros((L, n), dtype=torch.float64, device=dev)
             status = torch.zeros(1, dtype=torch.int32, device=dev)
-            qr(L, n, a0, tau, status)
             lam = gx.contiguous().clone()
-            adjoint_solve(L, n, d, a0, tau, A, lam, workspace(adjoint_workspace_bytes(L, n, d), dev), status)
+            _adjoint_solve_a0(L, n, d, a0, tau, A, lam, status)
             grad = torch.empty_like(cff)
             coef_grad(plan, x, lam, grad, ws)
             return grad, None, None, None, None

@@ -1072,12 +1072,14 @@ int md_adjoint_workspace_size(int prec, int n, int d, size_t *bytes) {
   return MD_OK;
 }
 
-int md_adjoint_solve(int prec, int n, int d, const double *qr, const double *tau, const double *A, double *g_lambda,
-                     void *ws, size_t ws_bytes, hipStream_t st, int32_t *dev_status) {
-  size_t need = 0;
-  if (md_adjoint_workspace_size(prec, n, d, &need) != MD_OK) return MD_EINVAL;
-  if (!qr || !tau || !g_lambda || (d > 0 && !A)) return fail(MD_EINVAL, "NULL argument");
-  if (!ws || ws_bytes < need) return fail(MD_ENOSPACE, "workspace too small");
+// The adjoint solve from the factors qr and tau, or from A_0 itself (a0, then
+// tau and qrs are scratch).
+static int adjoint_impl(int prec, int n, int d, const double *qr, double *a0, double *tau, void *qrs, const double *A,
+                        double *g_lambda, void *ws, size_t ws_bytes, hipStream_t st, int32_t *dev_status) {
+  size_t bytes = 0;
+  if (md_adjoint_workspace_size(prec, n, d, &bytes) != MD_OK) return MD_EINVAL;
+  if ((!qr && !a0) || !tau || !g_lambda || (d > 0 && !A)) return fail(MD_EINVAL, "NULL argument");
+  if (!ws || ws_bytes < bytes) return fail(MD_ENOSPACE, "workspace too small");
   const int L = prec, D = d + 1;
   const size_t nn = (size_t)n * n, nD = (size_t)n * D;
   size_t off = 0;
@@ -1092,7 +1094,17 @@ int md_adjoint_solve(int prec, int n, int d, const double *qr, const double *tau
          *lamT = take((size_t)L * nD);
   int *sync = reinterpret_cast<int *>(take(mdk::stages_sync_ints(D) / 2 + 1));
   hipError_t e;
-  if ((e = mdk::launch_form_m(L, n, qr, tau, invd, M, dev_status, st, nullptr, Nt)) != hipSuccess) return hip_fail(e, "form M");
+  int *need = nullptr;
+  if (a0) {  // M by refinement, else (decided on the device) by the factorization, in place
+    if (mdk::inverse_refined(L, n)) {
+      need = sync;  // (the staged solve takes its counters later)
+      if ((e = mdk::launch_inverse(L, n, a0, Nt, M, need, st)) != hipSuccess) return hip_fail(e, "inverse");
+    }
+    if ((e = run_qr(L, n, a0, tau, nullptr, dev_status, qrs, st, false, need)) != hipSuccess) return hip_fail(e, "qr");
+    qr = a0;
+  }
+  if ((e = mdk::launch_form_m(L, n, qr, tau, invd, M, dev_status, st, need, Nt)) != hipSuccess)
+    return hip_fail(e, "form M");
   if ((e = mdk::launch_transpose(L, M, Mt, n, n, nn, nn, st)) != hipSuccess) return hip_fail(e, "M^T");
   if ((e = mdk::launch_transpose(L, A, At, nn, D, nn * D, nn * D, st)) != hipSuccess) return hip_fail(e, "A^T");
   if ((e = mdk::launch_transpose(L * D, At, AtT, n, n, nn, nn, st)) != hipSuccess) return hip_fail(e, "A_k^T");
@@ -1103,6 +1115,25 @@ int md_adjoint_solve(int prec, int n, int d, const double *qr, const double *tau
     return hip_fail(e, "stages");
   if ((e = mdk::launch_rev_to_series(L, n, D, lamT, g_lambda, st)) != hipSuccess) return hip_fail(e, "reverse");
   return MD_OK;
+}
+
+int md_adjoint_solve(int prec, int n, int d, const double *qr, const double *tau, const double *A, double *g_lambda,
+                     void *ws, size_t ws_bytes, hipStream_t st, int32_t *dev_status) {
+  if (!qr) return fail(MD_EINVAL, "NULL argument");
+  return adjoint_impl(prec, n, d, qr, nullptr, const_cast<double *>(tau), nullptr, A, g_lambda, ws, ws_bytes, st,
+                      dev_status);
+}
+
+int md_adjoint_solve_a0(int prec, int n, int d, double *a0, double *tau, void *qr_ws, size_t qr_ws_bytes,
+                        const double *A, double *g_lambda, void *ws, size_t ws_bytes, hipStream_t st,
+                        int32_t *dev_status) {
+  if (!a0 || !qr_ws) return fail(MD_EINVAL, "NULL argument");
+  size_t bytes = 0;
+  if (md_qr_workspace_size(prec, n, &bytes) != MD_OK) return MD_EINVAL;
+  if (qr_ws_bytes < bytes) return fail(MD_ENOSPACE, "workspace too small");
+  hipError_t e = mdk::launch_status_init(dev_status, st);
+  if (e != hipSuccess) return hip_fail(e, "status");
+  return adjoint_impl(prec, n, d, nullptr, a0, tau, qr_ws, A, g_lambda, ws, ws_bytes, st, dev_status);
 }
 
 int md_coef_grad(const md_plan *p, const double *x, const double *lambda, double *grad_cff, void *ws, size_t ws_bytes,

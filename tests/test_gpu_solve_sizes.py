@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import mdinputs
+import oracle
 from gpu_helpers import TOL, dev, host
 
 pytestmark = pytest.mark.gpu
@@ -41,3 +42,37 @@ def test_residual_of_the_solution(L, n, D):
         for j in range(k + 1):
             size[:, k] += np.abs(A[0, :, :, j]) @ x[:, k - j]
     assert float((np.abs(host(r)[0]) / size).max()) <= TOL[L]
+
+
+@pytest.mark.parametrize("L,n", [(1, 6), (2, 1), (2, 33), (4, 16), (4, 65), (8, 9)])
+@pytest.mark.parametrize("cond", [1, 2.0**44])
+def test_adjoint_from_the_matrix(L, n, cond):
+    """The adjoint solve from A_0 (by refinement, or factorized where A_0 is ill
+    conditioned) against the one from its factors."""
+    import torch
+
+    import paper_2301_12659_amd as mdn
+
+    D = 6
+    rng = np.random.default_rng([L, n])
+    A = mdinputs.random_md(rng, L, (n, n, D), -1.0, 1.0)
+    i = np.arange(n)
+    A[0, i, i, 0] += 2.0 * n
+    if n > 1:
+        A[:, 0, :, 0] /= cond  # a row of A_0 far below the others
+    tA = dev(np.ascontiguousarray(A))
+    g = mdinputs.random_md(rng, L, (n, D), -1.0, 1.0)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    tau = torch.zeros((L, n), dtype=torch.float64, device="cuda")
+    a0 = tA[..., 0].clone(memory_format=torch.contiguous_format)
+    one, two = dev(g), dev(g)
+    mdn._adjoint_solve_a0(L, n, D - 1, a0, tau, tA, one, status)
+    a0 = tA[..., 0].clone(memory_format=torch.contiguous_format)
+    mdn.qr(L, n, a0, tau, status)
+    mdn.adjoint_solve(L, n, D - 1, a0, tau, tA, two, mdn.workspace(mdn.adjoint_workspace_bytes(L, n, D - 1)), status)
+    torch.cuda.synchronize()
+    assert int(status) == 0
+    x, y = host(one), host(two)
+    # every stage may carry the conditioning of A_0 once more
+    bound = TOL[L] * (float(cond) if n > 1 else 1.0) ** 2
+    assert float((oracle.absdiff(x, y) / np.maximum(np.abs(y[0]).max(axis=0), 1e-300)).max()) <= bound
