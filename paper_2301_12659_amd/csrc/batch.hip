@@ -40,6 +40,7 @@
 #include <string>
 #include <vector>
 
+#include "batch_tiles.hpp"
 #include "evaldiff_dev.hpp"
 #include "factor_dev.hpp"
 #include "inverse_dev.hpp"
@@ -159,15 +160,13 @@ __device__ __forceinline__ PathSlot<L, Ls> block_path(const BatchArgs &B, PathMe
 // unit is a tile of `tile_rows` entries (i, j) with all their coefficients,
 // turned through LDS so that both sides move whole cache lines, or 256
 // entries of b.  Bound by HBM.
-__host__ __device__ inline int tile_rows(int D) { return D <= 64 ? 16 : 8; }
-
 template <int L, int Ls>
 __global__ void __launch_bounds__(BATCH_NT) batch_assemble_kernel(BatchArgs B) {
   extern __shared__ double lds[];
   PathMeta pm;
   const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
   const int tid = threadIdx.x, NT = blockDim.x;
-  const int n = pm.n, D = pm.D, m = pm.m, nnz = pm.nnz, R = tile_rows(D), Rp = R + 1;
+  const int n = pm.n, D = pm.D, m = pm.m, nnz = pm.nnz, R = tile_rows(D);
   const size_t nn = (size_t)n * n, nD = (size_t)n * D, nnD = nn * D;
   const int32_t *poly_ptr = B.poly_ptr + pm.poly_off, *asm_ptr = B.asm_ptr + pm.asm_off;
   const int32_t *asm_ent = B.asm_ent + pm.asment_off;
@@ -191,7 +190,7 @@ __global__ void __launch_bounds__(BATCH_NT) batch_assemble_kernel(BatchArgs B) {
           }
         }
 #pragma unroll
-        for (int l = 0; l < Ls; ++l) lds[(l * D + s) * Rp + row] = acc[l];
+        for (int l = 0; l < Ls; ++l) lds[tile_index(D, l, s, row)] = acc[l];
         if (s == 0) st<Ls>(w.qr, nn, ij, acc);
       }
       __syncthreads();
@@ -199,7 +198,7 @@ __global__ void __launch_bounds__(BATCH_NT) batch_assemble_kernel(BatchArgs B) {
         const int s = q / R, row = q - s * R;
         if (row < rows)
 #pragma unroll
-          for (int l = 0; l < Ls; ++l) w.At[(size_t)l * nnD + (size_t)s * nn + ij0 + row] = lds[(l * D + s) * Rp + row];
+          for (int l = 0; l < Ls; ++l) w.At[(size_t)l * nnD + (size_t)s * nn + ij0 + row] = lds[tile_index(D, l, s, row)];
       }
       __syncthreads();
     } else {
@@ -470,6 +469,7 @@ struct BatchRun {
   struct Chunk {
     int first, count;  // entries of order
     int maxn, maxD;
+    int tile;          // doubles of LDS per limb of the assembly's tiles
     int work[BATCH_CLASSES], works[BATCH_CLASSES];  // first, number
   };
   std::vector<Chunk> chunks;
@@ -532,7 +532,7 @@ hipError_t build_run(const md_batch *b, const std::vector<int32_t> &list, BatchR
     const mdk::PathMeta &pm = b->meta[list[q]];
     const size_t bytes = align256(slot_doubles(b->L, b->L, pm.n, pm.D, pm.m, pm.nnz) * sizeof(double));
     if (used + bytes > budget) {
-      run.chunks.push_back({(int)q, 0, 0, 0, {}, {}});
+      run.chunks.push_back({(int)q, 0, 0, 0, 0, {}, {}});
       used = 0;
     }
     off[q] = (long long)used;
@@ -541,6 +541,7 @@ hipError_t build_run(const md_batch *b, const std::vector<int32_t> &list, BatchR
     ch.count++;
     ch.maxn = std::max(ch.maxn, pm.n);
     ch.maxD = std::max(ch.maxD, pm.D);
+    ch.tile = mdk::tile_doubles(ch.tile, pm.D);
   }
   for (BatchRun::Chunk &ch : run.chunks)
     for (int c = 0; c < BATCH_CLASSES; ++c) {
@@ -588,8 +589,8 @@ void launch_chunk(const mdk::BatchArgs &A, const BatchRun::Chunk &ch, const int2
   // few enough that small paths' empty workgroups do not count
   const int Y = std::max(16, std::min(256, 2048 / P));
   const dim3 NT(BATCH_NT), one(P), split(P, Y);
-  const size_t lds = (size_t)Ls * std::max(16 * 65, maxD > 64 ? 9 * maxD : 17 * maxD) * sizeof(double);
-  hipLaunchKernelGGL((batch_assemble_kernel<L, Ls>), split, NT, lds, st, B);
+  const size_t tile = (size_t)Ls * ch.tile * sizeof(double);
+  hipLaunchKernelGGL((batch_assemble_kernel<L, Ls>), split, NT, tile, st, B);
   hipLaunchKernelGGL((batch_inv64_kernel<L, Ls, 1, 8, 4>), one, dim3(256), 0, st, B, 0);
   if (maxn > 32) hipLaunchKernelGGL((batch_inv64_kernel<L, Ls, 1, 8, 8>), one, dim3(512), 0, st, B, 32);
   if (maxn > 64) hipLaunchKernelGGL((batch_inv64_kernel<L, Ls, 2, 8, 16>), one, dim3(1024), 0, st, B, 64);
