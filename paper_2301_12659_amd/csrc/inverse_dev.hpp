@@ -48,14 +48,14 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
 // pivot rows, every other column takes one update of rank NB,
 //     a_i := (i a pivot row of the panel ? 0 : a_i) + sum_m W[i][m] a_{p_m}.
 // One workgroup barrier per panel (the panels alternate between two
-// buffers).  Bound by the chain of the panel owners, 0.6 (n = 64) to 1 us (n = 128) per column
+// buffers); every wavefront returns after the same one.  Bound by the chain of the panel owners, 0.6 (n = 64) to 1 us (n = 128) per column
 // (a maximum over the lanes, lane reads, one division), where one column per
 // barrier with the rows spread over the wavefronts took 1.1 us (n = 64).
 template <int RW, int NB, int NW>
 __device__ void inv64_matrix(int n, const double *a, double *x, int *need) {
   constexpr int ROWS = 64 * RW;
   __shared__ double panel[2][NB][ROWS];
-  __shared__ int perm[NB * NW], where[ROWS], bad;
+  __shared__ int perm[NB * NW], where[ROWS], bad[2];
   __shared__ double red[2][NW];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -70,7 +70,6 @@ __device__ void inv64_matrix(int n, const double *a, double *x, int *need) {
       v[s][c] = (i < n && j < n) ? a[(size_t)i * n + j] : 0.0;
       na = __builtin_fma(v[s][c], v[s][c], na);
     }
-  if (tid == 0) bad = 0;
   bool used[RW];  // own rows that were pivots
 #pragma unroll
   for (int s = 0; s < RW; ++s) used[s] = lane + 64 * s >= n;
@@ -125,14 +124,17 @@ __device__ void inv64_matrix(int n, const double *a, double *x, int *need) {
           }
         }
       }
-      if (!ok && lane == 0) bad = 1;
+      if (lane == 0) bad[buf] = ok ? 0 : 1;
 #pragma unroll
       for (int s = 0; s < RW; ++s)
 #pragma unroll
         for (int m = 0; m < NB; ++m) panel[buf][m][lane + 64 * s] = v[s][m];
     }
     __syncthreads();
-    if (bad) {  // no pivot (the same decision in every wavefront)
+    // no pivot: the same decision in every wavefront, since the word alternates
+    // like the panels (the next owner may be done before the last wavefront
+    // reads this one; the one after next waits for the next barrier)
+    if (bad[buf]) {
       if (tid == 0) *need = 1;
       return;
     }
