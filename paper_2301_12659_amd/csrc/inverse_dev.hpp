@@ -266,18 +266,25 @@ __device__ __forceinline__ double residual_entry(int n, int v, int parts, bool d
   return s[0];
 }
 
+// What a residual of `limbs` limbs cannot tell from zero, relative to the size of
+// its terms: an omega below it does not measure the contraction to the next.
+__device__ __forceinline__ double refine_floor(int limbs) { return ldexp(1.0, 16 - 53 * limbs); }
+
 // Row j of M, y, by iterative refinement y += (e_j - y A_0) X from
 // the inverse X (x0) in doubles.  Rows, not columns: lane v then reads column v
 // of A_0 and X, row after row, coalesced.  blockDim.x = 64 ceil(n / 64) S: the
 // wavefronts split the n terms of a sum into S parts, added through LDS.  With
 // omega the largest entry of the residual relative to the size of its terms
-// and rho the contraction seen so far, the row is done once omega rho is
-// safely below the working precision: the correction just added was then
-// the last one that counts.  Early passes form the residual with only the
-// limbs they need; the last one takes one limb more than the working
-// precision (and y carries one more), so that M is A_0^{-1} rounded to L limbs,
-// without the rounding errors of a residual at L limbs, which cond(A_0) would
-// multiply.  A row that stops contracting raises *need.
+// and rho the contraction seen so far, this pass's omega over the one before
+// among it, the row is done once omega rho is safely below the working
+// precision: the correction just added was then the last one that counts.  (The
+// first omega alone says nothing of the contraction: it is about 2^-53
+// whatever the conditioning.  Ended on it, double-double rows were up to five
+// digits behind the factorization at cond(A_0) = 1e12.)  Early passes form the
+// residual with only the limbs they need; the last one takes one limb more than
+// the working precision (and y carries one more), so that M is A_0^{-1} rounded
+// to L limbs, without the rounding errors of a residual at L limbs, which
+// cond(A_0) would multiply.  A row that stops contracting raises *need.
 template <int L>
 struct RefineThreads {
   static constexpr int value = L == 8 ? 256 : 512;
@@ -298,6 +305,7 @@ __device__ void refine_row(int n, int S, int j, const double *a, const double *x
   __syncthreads();
   const double done = ldexp(1.0, -53 * L);
   double prev = 1.0, rho = 0.0;
+  int limbs = 1;  // of the residual before
   for (int pass = 0;; ++pass) {
     // the last pass that counts, if it contracts as those before it
     const bool last = pass > 0 && prev * rho * rho * 1024.0 <= done;
@@ -349,9 +357,11 @@ __device__ void refine_row(int n, int S, int j, const double *a, const double *x
       for (int l = 0; l < LX; ++l) ys[l * n + v] = s[l];
     }
     __syncthreads();
-    if (last && om * fmax(rho, 0x1p-53) * 64.0 <= done) break;
-    rho = fmax(rho, om / prev);
+    const double ratio = om / fmax(prev, refine_floor(limbs));
+    if (last && om * fmax(fmax(rho, ratio), 0x1p-53) * 64.0 <= done) break;
+    rho = fmax(rho, ratio);
     prev = om;
+    limbs = pass == 0 ? 2 : last ? LX : L == 8 && pass <= 2 ? 4 : L;
     if (!(rho <= 0x1p-8) || pass >= 8 * L) {  // not contracting (or not finite)
       if (tid == 0) atomicOr(need, 1);
       return;
