@@ -294,15 +294,18 @@ __device__ void refine_row(int n, int S, int j, const double *a, const double *x
   constexpr int LX = L + 1;  // limbs of y
   double *ys = lds, *es = lds + (size_t)LX * n, *part = es + n;  // part [S][LX + 1][n]
   __shared__ double red[2][8];
-  if (*need != 0) return;
+  __shared__ int stop;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int nw = blockDim.x >> 6, blocks = nw / S;
   const int split = w / blocks, v = (w - split * blocks) * 64 + lane;
   const bool col = v < n, lead = split == 0 && col;
   const int vv = col ? v : 0;
   const int i0 = split * n / S, i1 = (split + 1) * n / S;
+  // read once: other rows' workgroups may raise the word meanwhile
+  if (tid == 0) stop = *need;
   for (int q = tid; q < LX * n; q += blockDim.x) ys[q] = q < n ? x0[(size_t)j * n + q] : 0.0;
   __syncthreads();
+  if (stop != 0) return;
   const double done = ldexp(1.0, -53 * L);
   double prev = 1.0, rho = 0.0;
   int limbs = 1;  // of the residual before
