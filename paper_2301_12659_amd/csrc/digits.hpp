@@ -13,7 +13,7 @@
 // of the operands.  The precision is S digits less the two leading ones, which
 // may be short: 23 (S - 2) bits at worst, 437 for S = 21, with up to
 // S products of the last level and beyond dropped (about 2^4.5 units there).
-// Not-a-numbers and infinities give not-a-numbers.
+// Not-a-numbers and infinities give not-a-numbers, times a zero too.
 #pragma once
 #include "md.hpp"
 
@@ -24,8 +24,12 @@ constexpr double DIGIT_BASE = 8388608.0;       // 2^23
 constexpr double DIGIT_INV = 1.0 / 8388608.0;  // 2^-23
 // exponent of a zero: far below any other, so that its terms count as masked
 constexpr int DIGIT_ZERO = -100000;
-// exponent of a value that is not finite: above any other
-constexpr int DIGIT_NAN = 200;
+// exponent of a value that is not finite: so far above any other that its product
+// with a zero, a not-a-number, is above those of finite values
+constexpr int DIGIT_NAN = 200000;
+// exponent of an entry outside a series: its sum with any other, DIGIT_NAN among
+// them, is below that of two zeros
+constexpr int DIGIT_MASK = 8 * DIGIT_ZERO;
 
 template <int L> struct Digits;
 template <> struct Digits<8> { static constexpr int S = 21; };

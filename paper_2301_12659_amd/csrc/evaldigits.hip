@@ -37,7 +37,6 @@
 namespace mdk {
 
 constexpr int DIGIT_PAD = 3;
-constexpr int DIGIT_MASK = 4 * DIGIT_ZERO;
 
 // A series in LDS: digit p of coefficient s at d[p * Dp + s], its exponent r[s],
 // DIGIT_MASK for four entries ahead of the first and behind the last.
