@@ -509,6 +509,25 @@ int md_series_solve(int prec, int n, int d, const double *qr, const double *tau,
                            dev_status);
 }
 
+// Whether md_newton_steps can overlap the factorization of the next step
+// with the current one: plain steps whose staged solve is the persistent
+// kernel (its first stage is what the next-x_0 blocks reproduce) and whose A_0
+// comes from the coefficient-0 pre-pass.
+static bool steps_pipelined(const md_plan *p) {
+  return p->m > 0 && p->D > 1 && mdk::stages_persistent(p->L, p->n, p->D) &&
+         p->maxk <= mdk::evaldiff0_max_support(p->L);
+}
+
+// Whether a step forms M by refinement.  With more than 128 columns in quad
+// doubles that and the factorization take the same time (n = 150, 32
+// coefficients: 1837 and 1769 us a step), but where A_0 does not suit the
+// refinement both are run (2520 against 1456 us), so that it is taken there only
+// beside long monomials: their evaluation is what the factorization slows (the
+// triangular system of n = 160, 32 coefficients: 1722 against 2122).
+static bool step_refined(const md_plan *p, int Ls) {
+  return mdk::inverse_refined(Ls, p->n) && !(Ls == 4 && p->n > 128 && p->maxk <= mdk::evaldiff0_max_support(Ls));
+}
+
 // One Newton step with the residual b = -p(x) at the plan's precision L and
 // the Jacobian series, the QR of A_0 and the staged solve at Ls <= L limbs.
 // Limb-major storage makes the Ls-limb truncation of x, cff and b their
@@ -570,7 +589,7 @@ static int newton_step_impl(const md_plan *p, int Ls, int lo, int hi, bool keep_
     //    A_0 with Q^T and M = R^{-1} Q^T
     if ((e = hipEventRecord(p->fork, st)) != hipSuccess) return hip_fail(e, "fork");
     if ((e = hipStreamWaitEvent(p->aux, p->fork, 0)) != hipSuccess) return hip_fail(e, "fork wait");
-    int *need = mdk::inverse_refined(Ls, n) ? reinterpret_cast<int *>(at(ws, w.need)) : nullptr;
+    int *need = step_refined(p, Ls) ? reinterpret_cast<int *>(at(ws, w.need)) : nullptr;
     {
       Timed t(MD_CLASS_QR, p->aux);
       // (the inverse in doubles lies where Q^T would)
@@ -598,8 +617,12 @@ static int newton_step_impl(const md_plan *p, int Ls, int lo, int hi, bool keep_
   int *sync = reinterpret_cast<int *>(at(ws, w.sync));
   const mdk::TOut rt{r, lo, W, Ls}, atT{At, 0, W, Ls};
   const int nsync = mdk::stages_sync_ints(W);
-  // (a refined M leaves the QR to the matrices that need it)
-  const bool beside_qr = !keep_m && !mdk::inverse_refined(Ls, n);
+  // (a refined M leaves the QR to the matrices that need it; beside one, long
+  // monomials are what the step waits for, and they keep two teams of lanes:
+  // the triangular system of n = 200, 32 coefficients, quad double, 2780 us a
+  // step, 4940 with one worker a monomial; plans that md_newton_steps
+  // pipelines take the evaluation that it takes)
+  const bool beside_qr = pre0 && !step_refined(p, Ls) && !steps_pipelined(p);
   const size_t ndx = (size_t)Ls * n * W;
   if (!mixed) {
     int rc = eval_diff_impl(p, hi, cff, cst, x, b, A, ws, st, tsz, beside_qr, rt, atT, sync, nsync, dxT, ndx);
@@ -661,15 +684,6 @@ int md_newton_step(const md_plan *p, const double *cff, const double *cst, doubl
   return newton_step_impl(p, p->L, 0, p->D, false, cff, cst, x, dev_status, dev_norms, nullptr, ws, st);
 }
 
-// Whether md_newton_steps can overlap the factorization of the next step
-// with the current one: plain steps whose staged solve is the persistent
-// kernel (its first stage is what the next-x_0 blocks reproduce) and whose A_0
-// comes from the coefficient-0 pre-pass.
-static bool steps_pipelined(const md_plan *p) {
-  return p->m > 0 && p->D > 1 && mdk::stages_persistent(p->L, p->n, p->D) &&
-         p->maxk <= mdk::evaldiff0_max_support(p->L);
-}
-
 // count plain Newton steps.  A_0 of step s+1 depends on coefficient 0 of its
 // iterate only, x_0 + dx_0, and dx_0 = M r_0 is known once step s has M and
 // b: the launch of the products N, P, Q forms it too (bit for bit as the
@@ -694,7 +708,7 @@ static int newton_steps_impl(const md_plan *p, int count, const double *cff, con
   int *xseq = reinterpret_cast<int *>(at(ws, w.xseq)), *mseq = reinterpret_cast<int *>(at(ws, w.mseq));
   // M counted on the device only where the small back substitution forms it
   const bool mcount = n <= 64;
-  int *need = mdk::inverse_refined(L, n) ? reinterpret_cast<int *>(at(ws, w.need)) : nullptr;
+  int *need = step_refined(p, L) ? reinterpret_cast<int *>(at(ws, w.need)) : nullptr;
   if ((e = mdk::launch_status_init(dev_status, st, xseq, mseq)) != hipSuccess) return hip_fail(e, "status");
   double *b = at(ws, w.b), *A = at(ws, w.A), *r = at(ws, w.r), *dx = at(ws, w.dx), *N = at(ws, w.N);
   double *At = at(ws, w.At), *dxT = at(ws, w.dxT), *invd = at(ws, w.invd), *xn = at(ws, w.xn);

@@ -38,8 +38,13 @@ __global__ void __launch_bounds__(RefineThreads<L>::value) refine_kernel(int n, 
 }
 
 // Where the refinement replaces the factorization: at least two limbs, and
-// the matrix of doubles in the registers of one workgroup.
-bool inverse_refined(int L, int n) { return L >= 2 && n <= 192; }
+// the matrix of doubles in the registers of one workgroup.  From 129 columns on
+// those registers spill (8 us a column), and in double doubles the factorization
+// is faster: a step of n = 150, 16 coefficients, takes 806 us with it and 1292
+// with the refinement (n = 128: 647 and 287).  In quad doubles the refinement
+// stays the faster (the complex step of 2 n = 160: 2051 and 1804 us; a real one:
+// launch_inverse's callers), in octo doubles by far (n = 150: 9568 and 3272).
+bool inverse_refined(int L, int n) { return L >= 2 && n <= (L == 2 ? 128 : 192); }
 
 template <int L>
 static void launch_refine(int n, const double *a, const double *x0, double *M, int *need, hipStream_t st) {
