@@ -30,8 +30,8 @@ __global__ void __launch_bounds__(64 * NW) inv64_kernel(int n, const double *a, 
 }
 
 template <int L>
-__global__ void __launch_bounds__(RefineThreads<L>::value) refine_kernel(int n, int S, const double *a, const double *x0, double *M,
-                                                     int *need) {
+__global__ void __launch_bounds__(RefineThreads<L>::value, RefineThreads<L>::waves)
+    refine_kernel(int n, int S, const double *a, const double *x0, double *M, int *need) {
   extern __shared__ double lds[];
   __builtin_amdgcn_s_setprio(3);
   refine_row<L>(n, S, blockIdx.x, a, x0, M, need, lds);

@@ -285,9 +285,11 @@ __device__ __forceinline__ double refine_floor(int limbs) { return ldexp(1.0, 16
 // the working precision (and y carries one more), so that M is A_0^{-1} rounded
 // to L limbs, without the rounding errors of a residual at L limbs, which
 // cond(A_0) would multiply.  A row that stops contracting raises *need.
+// (waves: wavefronts a SIMD that the row's registers leave; a few registers more
+// and a quad-double batch takes a fifth longer)
 template <int L>
 struct RefineThreads {
-  static constexpr int value = L == 8 ? 256 : 512;
+  static constexpr int value = L == 8 ? 256 : 512, waves = L == 2 ? 5 : L == 4 ? 3 : 1;
 };
 template <int L>
 __device__ void refine_row(int n, int S, int j, const double *a, const double *x0, double *M, int *need, double *lds) {
