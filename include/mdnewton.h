@@ -323,7 +323,8 @@ int md_newton_step_complex(const md_plan *plan, const double *cff, const double 
  * dev_status[p] is the path's status (MD_OK, MD_ESINGULAR, MD_ENONFINITE),
  * dev_norms[2p] = max |b| and dev_norms[2p+1] = max |dx| over the path's
  * series (leading limbs).  The workspace (md_batch_workspace_size) holds the
- * intermediates of as many of the largest paths as two per compute unit.
+ * intermediates of as many of the largest paths as two per compute unit, or as
+ * fit 256 MB where those are more.
  * The call is asynchronous; it captures its launches in a graph on the
  * second call with the same arguments and replays the graph afterwards.
  * Not thread safe per batch.

@@ -17,8 +17,8 @@
 //     four: the stages of a block by one workgroup per path, the later
 //     right-hand sides by the whole grid;
 //   x := x + dx, norms and status.
-// The workspace is G (2 per CU) times the largest path's intermediates; paths
-// that do not fit it together are run in chunks.
+// The workspace is G times the largest path's intermediates (2 per CU, more of
+// small ones); paths that do not fit it together are run in chunks.
 // Measured (quad double, 1024 paths of n = 16..96, 16, 32 or 64 coefficients, 8
 // to 32 monomials per polynomial): 126 ms with the whole step of a path in one
 // workgroup, where the largest path, on its own at the end, was the bound;
@@ -160,18 +160,24 @@ __device__ __forceinline__ PathSlot<L, Ls> block_path(const BatchArgs &B, PathMe
 // unit is a tile of `tile_rows` entries (i, j) with all their coefficients,
 // turned through LDS so that both sides move whole cache lines, or 256
 // entries of b.  Bound by HBM.
+__host__ __device__ inline int assemble_tiles(int n, int D) { return (n * n + tile_rows(D) - 1) / tile_rows(D); }
+__host__ __device__ inline int assemble_units(int n, int D) {
+  return assemble_tiles(n, D) + (n * D + BATCH_NT - 1) / BATCH_NT;
+}
+
 template <int L, int Ls>
 __global__ void __launch_bounds__(BATCH_NT) batch_assemble_kernel(BatchArgs B) {
   extern __shared__ double lds[];
   PathMeta pm;
   const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
-  const int tid = threadIdx.x, NT = blockDim.x;
+  constexpr int NT = BATCH_NT;
+  const int tid = threadIdx.x;
   const int n = pm.n, D = pm.D, m = pm.m, nnz = pm.nnz, R = tile_rows(D);
   const size_t nn = (size_t)n * n, nD = (size_t)n * D, nnD = nn * D;
   const int32_t *poly_ptr = B.poly_ptr + pm.poly_off, *asm_ptr = B.asm_ptr + pm.asm_off;
   const int32_t *asm_ent = B.asm_ent + pm.asment_off;
   const double *cst = B.cst + pm.x_off;
-  const int tiles = (int)((nn + R - 1) / R), units = tiles + (int)((nD + NT - 1) / NT);
+  const int tiles = assemble_tiles(n, D), units = assemble_units(n, D);
   for (int unit = blockIdx.y; unit < units; unit += gridDim.y) {
     if (unit < tiles) {
       const int ij0 = unit * R, rows = min(R, (int)nn - ij0);
@@ -238,7 +244,8 @@ __global__ void __launch_bounds__(64 * NW) batch_inv64_kernel(BatchArgs B, int l
 }
 // (sizes lo < n <= hi; grid.y: rows)
 template <int L, int Ls>
-__global__ void __launch_bounds__(RefineThreads<Ls>::value) batch_refine_kernel(BatchArgs B, int lo, int hi, int S) {
+__global__ void __launch_bounds__(RefineThreads<Ls>::value, Ls == 4 ? 3 : 2)
+    batch_refine_kernel(BatchArgs B, int lo, int hi, int S) {
   extern __shared__ double lds[];
   PathMeta pm;
   const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
@@ -294,14 +301,14 @@ __global__ void __launch_bounds__(BATCH_NT) batch_n_kernel(BatchArgs B) {
 constexpr int BATCH_BLOCK = 4;
 
 template <int L, int Ls>
-__global__ void __launch_bounds__(512) batch_stages_kernel(BatchArgs B, int kb) {
+__global__ void __launch_bounds__(512) batch_stages_kernel(BatchArgs B, int kb, int len) {
   PathMeta pm;
   const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
   const int n = pm.n, D = pm.D;
   if (kb >= D) return;
   const int T = B.tile[pm.bucket], nteams = blockDim.x / T, team = threadIdx.x / T, tl = threadIdx.x % T;
   const size_t nn = (size_t)n * n, nD = (size_t)n * D, nnD = nn * D;
-  const int kend = min(kb + BATCH_BLOCK, D);
+  const int kend = min(kb + len, D);
   for (int k = kb; k < kend; ++k) {
     for (int i = team; i < n; i += nteams) {
       double acc[Ls], s2[Ls];
@@ -352,6 +359,11 @@ __global__ void __launch_bounds__(512) batch_stages_kernel(BatchArgs B, int kb) 
 // ... then all later right-hand sides, r_m -= sum over the block's stages k of
 // A_{m-k} dx_k, by the whole grid.  A task is a row of BATCH_BLOCK neighbouring
 // r_m: it reads 7 entries of A for 16 multiply-adds.
+__host__ __device__ inline int update_tasks(int n, int D, int kb) {
+  const int first = kb + BATCH_BLOCK;
+  return first < D ? n * ((D - first + BATCH_BLOCK - 1) / BATCH_BLOCK) : 0;
+}
+
 template <int L, int Ls>
 __global__ void __launch_bounds__(BATCH_NT) batch_update_kernel(BatchArgs B, int kb) {
   constexpr int K = BATCH_BLOCK;
@@ -361,7 +373,7 @@ __global__ void __launch_bounds__(BATCH_NT) batch_update_kernel(BatchArgs B, int
   if (first >= D) return;
   const int T = B.tile[pm.bucket], nteams = blockDim.x / T, tl = threadIdx.x % T;
   const size_t nn = (size_t)n * n, nD = (size_t)n * D, nnD = nn * D;
-  const int ntask = n * ((D - first + K - 1) / K);
+  const int ntask = update_tasks(n, D, kb);
   for (int task = blockIdx.y * nteams + threadIdx.x / T; task < ntask; task += gridDim.y * nteams) {
     const int g = task / n, i = task - g * n, m0 = first + K * g, a0 = m0 - kb - (K - 1);
     double acc[K][Ls];
@@ -470,6 +482,7 @@ struct BatchRun {
     int first, count;  // entries of order
     int maxn, maxD;
     int tile;          // doubles of LDS per limb of the assembly's tiles
+    int asm_units, update_tasks;  // the most of a path: units of the assembly, rows of the first update
     int work[BATCH_CLASSES], works[BATCH_CLASSES];  // first, number
   };
   std::vector<Chunk> chunks;
@@ -532,7 +545,7 @@ hipError_t build_run(const md_batch *b, const std::vector<int32_t> &list, BatchR
     const mdk::PathMeta &pm = b->meta[list[q]];
     const size_t bytes = align256(slot_doubles(b->L, b->L, pm.n, pm.D, pm.m, pm.nnz) * sizeof(double));
     if (used + bytes > budget) {
-      run.chunks.push_back({(int)q, 0, 0, 0, 0, {}, {}});
+      run.chunks.push_back({(int)q, 0, 0, 0, 0, 0, 0, {}, {}});
       used = 0;
     }
     off[q] = (long long)used;
@@ -542,6 +555,8 @@ hipError_t build_run(const md_batch *b, const std::vector<int32_t> &list, BatchR
     ch.maxn = std::max(ch.maxn, pm.n);
     ch.maxD = std::max(ch.maxD, pm.D);
     ch.tile = mdk::tile_doubles(ch.tile, pm.D);
+    ch.asm_units = std::max(ch.asm_units, mdk::assemble_units(pm.n, pm.D));
+    ch.update_tasks = std::max(ch.update_tasks, mdk::update_tasks(pm.n, pm.D, 0));
   }
   for (BatchRun::Chunk &ch : run.chunks)
     for (int c = 0; c < BATCH_CLASSES; ++c) {
@@ -588,27 +603,42 @@ void launch_chunk(const mdk::BatchArgs &A, const BatchRun::Chunk &ch, const int2
   // workgroups per path: enough to spread a chunk of few paths over the chip,
   // few enough that small paths' empty workgroups do not count
   const int Y = std::max(16, std::min(256, 2048 / P));
-  const dim3 NT(BATCH_NT), one(P), split(P, Y);
+  const dim3 NT(BATCH_NT), one(P);
+  // (and no more than the largest path has work for)
+  auto split = [&](int most) { return dim3(P, std::max(1, std::min(Y, most))); };
+  constexpr int TEAMS = BATCH_NT / 16;  // (16 lanes a team, the widest tile)
   const size_t tile = (size_t)Ls * ch.tile * sizeof(double);
-  hipLaunchKernelGGL((batch_assemble_kernel<L, Ls>), split, NT, tile, st, B);
+  hipLaunchKernelGGL((batch_assemble_kernel<L, Ls>), split(ch.asm_units), NT, tile, st, B);
   hipLaunchKernelGGL((batch_inv64_kernel<L, Ls, 1, 8, 4>), one, dim3(256), 0, st, B, 0);
   if (maxn > 32) hipLaunchKernelGGL((batch_inv64_kernel<L, Ls, 1, 8, 8>), one, dim3(512), 0, st, B, 32);
   if (maxn > 64) hipLaunchKernelGGL((batch_inv64_kernel<L, Ls, 2, 8, 16>), one, dim3(1024), 0, st, B, 64);
   auto refine = [&](int lo, int hi) {
     const int n = std::min(hi, maxn);
     // rows enough to fill the chip without splitting a row's sums (1024 paths:
-    // 16.5 ms in four parts, 11.0 in one)
-    const int S = (long long)P * n >= 4096 ? 1 : refine_parts<Ls>(n);
+    // 16.5 ms in four parts, 11.0 in one), or short sums, where parts are wavefronts
+    // that do not find room at once (512 paths of n = 4, double double: 25 us in
+    // four parts, 9 in one)
+    const long long rows = (long long)P * n;
+    int S = rows >= 4096 ? 1 : refine_parts<Ls>(n);
+    if (n < 16) S = std::max(1, std::min(S, (int)(3072 / rows)));
     hipLaunchKernelGGL((batch_refine_kernel<L, Ls>), dim3(P, n), dim3(64 * ((n + 63) / 64) * S), refine_lds<Ls>(n, S), st,
                        B, lo, hi, S);
   };
   refine(0, 64);
   if (maxn > 64) refine(64, 128);
   hipLaunchKernelGGL((batch_factor_kernel<L, Ls>), one, NT, 0, st, B);
-  if (maxD > 1) hipLaunchKernelGGL((batch_n_kernel<L, Ls>), split, NT, 0, st, B);
-  for (int kb = 0; kb < maxD; kb += BATCH_BLOCK) {
-    hipLaunchKernelGGL((batch_stages_kernel<L, Ls>), one, dim3(512), 0, st, B, kb);
-    if (kb + BATCH_BLOCK < maxD) hipLaunchKernelGGL((batch_update_kernel<L, Ls>), split, NT, 0, st, B, kb);
+  if (maxD > 1) hipLaunchKernelGGL((batch_n_kernel<L, Ls>), split((maxn * maxn + TEAMS - 1) / TEAMS), NT, 0, st, B);
+  // a stage's rows by one workgroup: no more wavefronts than rows of 16 lanes
+  // (512 paths of n = 4, 8 coefficients, quad double: 46 us with 512 threads, 25 with 64)
+  const dim3 rows(std::min(512, (maxn * 16 + 63) / 64 * 64));
+  // one block of all stages where that takes less than the launches of several:
+  // 512 paths of n = 4, 8 coefficients, double double, 68 us a step against 71; of
+  // n = 8, 16 coefficients 146 against 137
+  const int len = (maxn <= 16 && maxD <= 8) || maxn * maxD <= 32 ? maxD : BATCH_BLOCK;
+  for (int kb = 0; kb < maxD; kb += len) {
+    hipLaunchKernelGGL((batch_stages_kernel<L, Ls>), one, rows, 0, st, B, kb, len);
+    if (kb + len < maxD)
+      hipLaunchKernelGGL((batch_update_kernel<L, Ls>), split((ch.update_tasks + TEAMS - 1) / TEAMS), NT, 0, st, B, kb);
   }
   hipLaunchKernelGGL((batch_finish_kernel<L, Ls>), one, NT, 0, st, B);
 }
@@ -764,7 +794,12 @@ int md_batch_create(int prec, int npaths, const int32_t *n, const int32_t *d, co
     delete b;
     return mdk::api_hip_fail(e, "device query");
   }
-  b->G = std::min(npaths, 2 * std::max(cus, 1));
+  // two of the largest paths per compute unit fill the chip; of smaller ones, as
+  // many as 256 MB hold, since every chunk is a pass over all launches (8192
+  // paths of n = 4, 8 coefficients, double double: 1373 us in 16 chunks with 16
+  // workgroups a path throughout, 524 in one with as many as there is work for)
+  const size_t fit = ((size_t)256 << 20) / b->slot_bytes;
+  b->G = (int)std::min<size_t>(npaths, std::max<size_t>(2 * std::max(cus, 1), fit));
   // device tables: meta, order, tile, then the int tables
   const size_t nt = tab_poly.size() + tab_mon.size() + tab_var.size() + tab_exp.size() + tab_asm.size() +
                     tab_asment.size();
