@@ -273,9 +273,7 @@ __global__ void __launch_bounds__(BATCH_NT) batch_factor_kernel(BatchArgs B) {
 
 // 4. N = M A_1.
 template <int L, int Ls>
-__global__ void __launch_bounds__(BATCH_NT) batch_n_kernel(BatchArgs B) {
-  PathMeta pm;
-  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+__device__ __forceinline__ void form_n(const BatchArgs &B, const PathMeta &pm, const PathSlot<L, Ls> &w) {
   if (pm.D <= 1) return;
   const int n = pm.n, T = B.tile[pm.bucket], nteams = blockDim.x / T, tl = threadIdx.x % T;
   const size_t nn = (size_t)n * n, nnD = nn * pm.D;
@@ -294,6 +292,12 @@ __global__ void __launch_bounds__(BATCH_NT) batch_n_kernel(BatchArgs B) {
     if (tl == 0) st<Ls>(w.N, nn, (size_t)i * n + j, s2);
   }
 }
+template <int L, int Ls>
+__global__ void __launch_bounds__(BATCH_NT) batch_n_kernel(BatchArgs B) {
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  form_n<L, Ls>(B, pm, w);
+}
 
 // 5. Stages in blocks of BATCH_BLOCK: the block's own stages by one workgroup
 // per path, dx_k = M r_k - N dx_{k-1} and r_m -= A_{m-k} dx_k for the later m of
@@ -301,14 +305,11 @@ __global__ void __launch_bounds__(BATCH_NT) batch_n_kernel(BatchArgs B) {
 constexpr int BATCH_BLOCK = 4;
 
 template <int L, int Ls>
-__global__ void __launch_bounds__(512) batch_stages_kernel(BatchArgs B, int kb, int len) {
-  PathMeta pm;
-  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+__device__ __forceinline__ void solve_stages(const BatchArgs &B, const PathMeta &pm, const PathSlot<L, Ls> &w, int kb,
+                                             int kend) {
   const int n = pm.n, D = pm.D;
-  if (kb >= D) return;
   const int T = B.tile[pm.bucket], nteams = blockDim.x / T, team = threadIdx.x / T, tl = threadIdx.x % T;
   const size_t nn = (size_t)n * n, nD = (size_t)n * D, nnD = nn * D;
-  const int kend = min(kb + len, D);
   for (int k = kb; k < kend; ++k) {
     for (int i = team; i < n; i += nteams) {
       double acc[Ls], s2[Ls];
@@ -354,6 +355,13 @@ __global__ void __launch_bounds__(512) batch_stages_kernel(BatchArgs B, int kb, 
     }
     __syncthreads();
   }
+}
+
+template <int L, int Ls>
+__global__ void __launch_bounds__(512) batch_stages_kernel(BatchArgs B, int kb) {
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  if (kb < pm.D) solve_stages<L, Ls>(B, pm, w, kb, min(kb + BATCH_BLOCK, pm.D));
 }
 
 // ... then all later right-hand sides, r_m -= sum over the block's stages k of
@@ -413,10 +421,8 @@ __global__ void __launch_bounds__(BATCH_NT) batch_update_kernel(BatchArgs B, int
 
 // 6. x := x + dx, norms and status.
 template <int L, int Ls>
-__global__ void __launch_bounds__(BATCH_NT) batch_finish_kernel(BatchArgs B) {
-  __shared__ double shr[BATCH_NT / 64];
-  PathMeta pm;
-  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+__device__ __forceinline__ void finish_path(const BatchArgs &B, const PathMeta &pm, const PathSlot<L, Ls> &w,
+                                            double *shr) {
   const int tid = threadIdx.x, NT = blockDim.x, n = pm.n, D = pm.D, p = B.order[blockIdx.x];
   const size_t nD = (size_t)n * D;
   double *x = B.x + pm.x_off;
@@ -446,6 +452,30 @@ __global__ void __launch_bounds__(BATCH_NT) batch_finish_kernel(BatchArgs B) {
     B.status[p] = path_need(w)[1] ? MD_ESINGULAR : (fin > 0.0 ? MD_ENONFINITE : MD_OK);
   }
 }
+template <int L, int Ls>
+__global__ void __launch_bounds__(BATCH_NT) batch_finish_kernel(BatchArgs B) {
+  __shared__ double shr[BATCH_NT / 64];
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  finish_path<L, Ls>(B, pm, w, shr);
+}
+
+// 4., 5. and 6. of small systems with few coefficients in one launch, a
+// workgroup per path: as launches they take 4 to 5 us each, however little there
+// is to do (64 paths of n = 2, 16 coefficients, double double: 68 us a step, 80
+// with them apart; two of n = 4, 16 coefficients, quad double: 157 and 141).
+template <int L, int Ls>
+__global__ void __launch_bounds__(BATCH_NT) batch_small_kernel(BatchArgs B) {
+  __shared__ double shr[BATCH_NT / 64];
+  PathMeta pm;
+  const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
+  form_n<L, Ls>(B, pm, w);
+  __syncthreads();
+  solve_stages<L, Ls>(B, pm, w, 0, pm.D);
+  __syncthreads();
+  finish_path<L, Ls>(B, pm, w, shr);
+}
+bool batch_small(int n, int D) { return D <= 8 ? n <= 8 : D <= 16 && n <= 3; }
 
 template <int L, int Ls, int LIMBS, int G2>
 void launch_batch_eval(const BatchArgs &A, const int2 *work, int count, hipStream_t st) {
@@ -620,24 +650,24 @@ void launch_chunk(const mdk::BatchArgs &A, const BatchRun::Chunk &ch, const int2
     // four parts, 9 in one)
     const long long rows = (long long)P * n;
     int S = rows >= 4096 ? 1 : refine_parts<Ls>(n);
-    if (n < 16) S = std::max(1, std::min(S, (int)(3072 / rows)));
+    if (n < 16) S = std::max(1, std::min(S, (int)(1024 * (Ls == 4 ? 3 : 2) / rows)));
     hipLaunchKernelGGL((batch_refine_kernel<L, Ls>), dim3(P, n), dim3(64 * ((n + 63) / 64) * S), refine_lds<Ls>(n, S), st,
                        B, lo, hi, S);
   };
   refine(0, 64);
   if (maxn > 64) refine(64, 128);
   hipLaunchKernelGGL((batch_factor_kernel<L, Ls>), one, NT, 0, st, B);
-  if (maxD > 1) hipLaunchKernelGGL((batch_n_kernel<L, Ls>), split((maxn * maxn + TEAMS - 1) / TEAMS), NT, 0, st, B);
   // a stage's rows by one workgroup: no more wavefronts than rows of 16 lanes
   // (512 paths of n = 4, 8 coefficients, quad double: 46 us with 512 threads, 25 with 64)
-  const dim3 rows(std::min(512, (maxn * 16 + 63) / 64 * 64));
-  // one block of all stages where that takes less than the launches of several:
-  // 512 paths of n = 4, 8 coefficients, double double, 68 us a step against 71; of
-  // n = 8, 16 coefficients 146 against 137
-  const int len = (maxn <= 16 && maxD <= 8) || maxn * maxD <= 32 ? maxD : BATCH_BLOCK;
-  for (int kb = 0; kb < maxD; kb += len) {
-    hipLaunchKernelGGL((batch_stages_kernel<L, Ls>), one, rows, 0, st, B, kb, len);
-    if (kb + len < maxD)
+  auto rows = [&](int most) { return dim3(std::min(most, (maxn * 16 + 63) / 64 * 64)); };
+  if (batch_small(maxn, maxD)) {
+    hipLaunchKernelGGL((batch_small_kernel<L, Ls>), one, rows(BATCH_NT), 0, st, B);
+    return;
+  }
+  if (maxD > 1) hipLaunchKernelGGL((batch_n_kernel<L, Ls>), split((maxn * maxn + TEAMS - 1) / TEAMS), NT, 0, st, B);
+  for (int kb = 0; kb < maxD; kb += BATCH_BLOCK) {
+    hipLaunchKernelGGL((batch_stages_kernel<L, Ls>), one, rows(512), 0, st, B, kb);
+    if (kb + BATCH_BLOCK < maxD)
       hipLaunchKernelGGL((batch_update_kernel<L, Ls>), split((ch.update_tasks + TEAMS - 1) / TEAMS), NT, 0, st, B, kb);
   }
   hipLaunchKernelGGL((batch_finish_kernel<L, Ls>), one, NT, 0, st, B);
