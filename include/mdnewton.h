@@ -162,7 +162,8 @@ int md_newton_step(const md_plan *plan, const double *cff, const double *cst, do
  * staged solve of step s and the evaluation of step s+1 (M is formed for
  * every step; Section 5.3 factorizes once per path).
  * This applies to plans whose staged solve runs in one persistent launch
- * (double double n <= 192, quad double n <= 128) with supports of at most 8 variables;
+ * (double double n <= 192, quad double n <= 128, fewer with very many
+ * coefficients), at most 65536 monomials and supports of at most 8 variables;
  * other plans take count ordinary steps.  The factorization of step s+1
  * waits on the device for the launch that forms its x_0 on the caller's
  * stream, and the caller's stream for M of each step (counters in the

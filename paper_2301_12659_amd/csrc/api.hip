@@ -512,10 +512,15 @@ int md_series_solve(int prec, int n, int d, const double *qr, const double *tau,
 // Whether md_newton_steps can overlap the factorization of the next step
 // with the current one: plain steps whose staged solve is the persistent
 // kernel (its first stage is what the next-x_0 blocks reproduce) and whose A_0
-// comes from the coefficient-0 pre-pass.
+// comes from the coefficient-0 pre-pass.  The pre-pass's workgroups, one per 64
+// monomials, wait on the device for the launch that forms x_0: they must leave
+// room for that launch and those ahead of it on the caller's stream, and the
+// chip holds 3072 of them in quad doubles.  A third of that is the limit; with
+// so many monomials the evaluation is all of a step's time in any case.
+constexpr int MAX_WAITING_GROUPS = 1024;
 static bool steps_pipelined(const md_plan *p) {
   return p->m > 0 && p->D > 1 && mdk::stages_persistent(p->L, p->n, p->D) &&
-         p->maxk <= mdk::evaldiff0_max_support(p->L);
+         p->maxk <= mdk::evaldiff0_max_support(p->L) && p->m <= 64 * MAX_WAITING_GROUPS;
 }
 
 // Whether a step forms M by refinement.  With more than 128 columns in quad

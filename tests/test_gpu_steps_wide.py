@@ -78,3 +78,10 @@ def test_solve_with_many_coefficients(L, n, D):
         for j in range(k + 1):
             size[:, k] += np.abs(A[0, :, :, j]) @ x[:, k - j]
     assert float((np.abs(host(r)[0]) / size).max()) <= TOL[L]
+
+
+@pytest.mark.parametrize("L,mons", [(2, 1007), (2, 1009), (4, 1009)])  # 65 (mons + 1) monomials: about 64 x 1024
+def test_bit_identical_with_many_monomials(L, mons):
+    s = mdinputs.make_system("many", L, 65, 1, mons, 1, 3, (1,), 3, None, boost=True, damping=0.25, boost_gamma=2.0,
+                             vectorized=True)
+    compare(s, mdinputs.random_constant(s, 1), 3)
