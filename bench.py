@@ -5,7 +5,7 @@ Workload: n = 64 polynomials in 64 variables, truncation degree d = 63
 (D = 64 coefficients), quad double; 32 monomials of 2..6 variables with
 exponents in {1, 2} per polynomial plus a diagonal boost; seeded synthetic
 data (mdinputs.medium_qd).  A step is one full md_newton_step: evaluation
-and differentiation by convolutions, assembly, Householder QR of A_0, the
+and differentiation by convolutions, assembly, the inverse of A_0, the
 staged block Toeplitz solve and the update, on inputs resident on the GPU.
 
 Prints one JSON line.  --gpus above 1 is refused: this build runs on one GPU.
@@ -29,7 +29,7 @@ PEAK_FP64_TFLOPS = 78.6  # MI355X FP64 vector, FMA = 2 flops
 # traffic recorded from hardware counters is reported only while they are
 # unchanged since the counters were taken
 _EVALDIFF_SOURCES = ("evaldiff.hip", "evaldiff_dev.hpp", "evalargs.hpp", "common.hpp", "md.hpp", "md_gen.inc")
-_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "evaldiff_pair_kernel_medium_qd_hbm_traffic.md")
+_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "evaldiff_team_kernel_medium_qd_hbm_traffic.md")
 
 
 def evaldiff_source_sha256():
@@ -56,7 +56,7 @@ def _recorded_traffic():
     return int(kv["fetch_bytes_per_launch"]) + int(kv["write_bytes_per_launch"])
 
 
-_SQ_FILE = os.path.join(ROOT, "profiles", "evaldiff_pair_kernel_medium_qd_sq_counters.md")
+_SQ_FILE = os.path.join(ROOT, "profiles", "evaldiff_team_kernel_medium_qd_sq_counters.md")
 
 
 def _recorded_sq():
@@ -95,7 +95,7 @@ def _bench_batch(mdn, torch, np, mdinputs, npaths, steps):
     16..96, d in {15, 31, 63}, 8..32 monomials per polynomial of 2..5
     variables with exponent 1, manufactured solutions (constants evaluated on
     the GPU); plain steps and qd residual / dd solve steps, each a graph
-    replay of one persistent launch."""
+    replay of the launches over all paths."""
     paths = mdinputs.batch_paths(npaths, 4)
     b = mdn.Batch(paths)
     dev = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device="cuda")
@@ -222,7 +222,7 @@ def _bench_configs(mdn, torch, np, mdinputs, reps):
                     times.append(e0.elapsed_time(e1))
                 cff.grad = None
             r["backward_ms"] = round(min(times), 4)
-            r["backward"] = ("A(t) at the solution, QR of A_0, the transposed staged solve and the coefficient "
+            r["backward"] = ("A(t) at the solution, A_0^-1, the transposed staged solve and the coefficient "
                              "gradients (%d monomial coefficients)" % s.m)
         res[name] = r
         del drv
@@ -598,7 +598,7 @@ def main():
     status = drv.status_code()
     err_manufactured = _err_vs(mdn, torch, drv.x, xstar)
 
-    # the same number of single md_newton_step calls (QR on the critical path)
+    # the same number of single md_newton_step calls (A_0^-1 on the critical path)
     e0.record()
     for _ in range(args.steps):
         drv.step()
@@ -651,7 +651,7 @@ def main():
         conventions.update({
             "executed_tflops": round(ex / t / 1e12, 3), "executed_frac": round(ex / t / 1e12 / PEAK_FP64_TFLOPS, 4),
             "fp64_pipe_utilization": round(lane_ops / (64.0 * 256 * 2.4e9 * t), 4),
-            "counters": "profiles/evaldiff_pair_kernel_medium_qd_sq_counters.md (same kernel sources)"})
+            "counters": "profiles/evaldiff_team_kernel_medium_qd_sq_counters.md (same kernel sources)"})
     else:
         conventions.update({"executed_tflops": None, "fp64_pipe_utilization": None,
                             "counters": "no SQ counters recorded for the current kernel sources"})

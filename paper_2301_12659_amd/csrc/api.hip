@@ -425,10 +425,9 @@ static void eval_args(const md_plan *p, const double *cff, const double *x, void
 // b and A for the first Dc coefficients (the problem truncated at order Dc);
 // tsz (nullable) gets the sizes of the terms of b.  beside_qr: the launch
 // runs beside the QR of a Newton step, off the critical path; the evaluation
-// then takes one wavefront per monomial, which leaves the QR's wavefronts
-// more issue slots on the CUs they share (measured: 0.966 against 0.981 ms
-// per medium quad-double step), while alone two wavefronts per monomial are
-// faster (353 against 403 us).
+// then takes one worker per monomial, which leaves the QR's wavefronts more
+// issue slots on the CUs they share (quad double, n = 200, 32 coefficients, 16
+// monomials a polynomial: 2497 us a step, 2868 with two teams).
 static int eval_diff_impl(const md_plan *p, int Dc, const double *cff, const double *cst, const double *x, double *b,
                           double *A, void *ws, hipStream_t st, double *tsz = nullptr, bool beside_qr = false,
                           mdk::TOut rt = mdk::TOut(), mdk::TOut aT = mdk::TOut(), int *clear = nullptr,

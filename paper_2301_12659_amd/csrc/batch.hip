@@ -524,7 +524,7 @@ struct BatchRun {
 
 struct md_batch {
   int L, P, G;
-  int maxn, maxD, maxm, maxnnz;
+  int maxn, maxD;
   std::vector<mdk::PathMeta> meta;
   std::vector<int32_t> order;             // all paths, most expensive first
   std::vector<double> cost;
@@ -716,7 +716,7 @@ int md_batch_create(int prec, int npaths, const int32_t *n, const int32_t *d, co
   md_batch *b = new md_batch();
   b->L = prec;
   b->P = npaths;
-  b->maxn = b->maxD = b->maxm = b->maxnnz = 0;
+  b->maxn = b->maxD = 0;
   std::vector<int32_t> tab_poly, tab_mon, tab_var, tab_exp, tab_asm, tab_asment;
   long long xo = 0, co = 0;
   size_t poly_o = 0, mon_o = 0, ent_o = 0;
@@ -798,8 +798,6 @@ int md_batch_create(int prec, int npaths, const int32_t *n, const int32_t *d, co
     b->cost.push_back(cost);
     b->maxn = std::max(b->maxn, np);
     b->maxD = std::max(b->maxD, Dp);
-    b->maxm = std::max(b->maxm, mp);
-    b->maxnnz = std::max(b->maxnnz, nnz);
     xo += (long long)np * Dp;
     co += mp;
     poly_o += np + 1;
@@ -902,8 +900,9 @@ int md_batch_newton_step(md_batch *b, int prec_solve, const double *cff, const d
   if (!(prec_solve == b->L || (b->L == MD_QD && prec_solve == MD_DD)))
     return mdk::api_fail(MD_EINVAL, "solve precision: the batch's, or double double under quad double");
   if (!ws || ws_bytes < batch_ws_bytes(b)) return mdk::api_fail(MD_ENOSPACE, "workspace too small");
-  // the step is two launches, replayed from a captured graph while the
-  // arguments stay the same (captured on the second call with them)
+  // the step's launches, some forty for paths of 64 coefficients, are replayed from
+  // a captured graph while the arguments stay the same (captured on the second
+  // call with them)
   const void *key[8] = {cff, cst, x, dev_status, dev_norms, ws, nullptr, nullptr};
   bool same = b->key_prec == prec_solve;
   for (int q = 0; q < 8; ++q) same = same && key[q] == b->key[q];

@@ -5,7 +5,7 @@
 // assemble.hip.
 //
 // Work decomposition.  Two teams of lanes per monomial (evaldiff_team_kernel);
-// beside a running QR, and in the batched step, one "worker", a group of G
+// beside a running QR, where monomials are short, one "worker", a group of G
 // lanes of one wavefront, which evaluates and differentiates one whole
 // monomial, product after product, with three series buffers in LDS.  In a
 // truncated product c_s = sum_{i<=s} a_i b_{s-i} the outputs are paired, s and

@@ -123,9 +123,10 @@ hipError_t launch_transpose_ld(int L, const double *in, size_t in_ld, double *ou
 hipError_t launch_gemm(int L, int n, const double *M, const double *B, size_t b_ls, double *out, int count,
                        hipStream_t st);
 // Staged solve of the block Toeplitz system on coefficient-major arrays.
-// NP holds N = M A_1 and, when stages_products() is 2, P = M A_2 after it
-// (L n^2 doubles each); sync is scratch of stages_sync_ints(D) ints.  One
-// persistent launch when stages_persistent(), else one launch per stage.
+// NP holds N = M A_1 and, as stages_products() says, P = M A_2 and Q = M A_3 after
+// it (L n^2 doubles each); sync is scratch of stages_sync_ints(D) ints.  One
+// workgroup for small systems, one persistent launch when stages_persistent(),
+// else one launch per stage.
 bool stages_persistent(int L, int n, int D);
 int stages_sync_ints(int D);
 int stages_products(int L, int n, int D);
