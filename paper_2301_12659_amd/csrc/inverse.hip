@@ -43,8 +43,8 @@ __global__ void __launch_bounds__(RefineThreads<L>::value, RefineThreads<L>::wav
 
 // Where the refinement replaces the factorization: at least two limbs, and
 // the matrix of doubles in the registers of one workgroup.  From 129 columns on
-// those registers spill (8 us a column), and in double doubles the factorization
-// is faster: a step of n = 150, 16 coefficients, takes 806 us with it and 1292
+// they have no room for the factors of a panel (7.5 us a column), and in double
+// doubles the factorization is faster: a step of n = 150, 16 coefficients, takes 806 us with it and 1292
 // with the refinement (n = 128: 647 and 287).  In quad doubles the refinement
 // stays the faster (the complex step of 2 n = 160: 2051 and 1804 us; a real one:
 // launch_inverse's callers), in octo doubles by far (n = 150: 9568 and 3272).

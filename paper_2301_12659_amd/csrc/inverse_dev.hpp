@@ -48,9 +48,11 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
 // pivot rows, every other column takes one update of rank NB,
 //     a_i := (i a pivot row of the panel ? 0 : a_i) + sum_m W[i][m] a_{p_m}.
 // One workgroup barrier per panel (the panels alternate between two
-// buffers); every wavefront returns after the same one.  Bound by the chain of the panel owners, 0.6 (n = 64) to 1 us (n = 128) per column
-// (a maximum over the lanes, lane reads, one division), where one column per
-// barrier with the rows spread over the wavefronts took 1.1 us (n = 64).
+// buffers); every wavefront returns after the same one.  Bound by the chain of
+// the panel owners, 0.6 (n = 64) to 1 us (n = 128) per column (a maximum over the
+// lanes, lane reads, one division), where one column per barrier with the rows
+// spread over the wavefronts took 1.1 us (n = 64); with three rows a lane it is
+// 7.5 us (n = 160: 1.2 ms), the factors read from LDS for every entry.
 template <int RW, int NB, int NW>
 __device__ void inv64_matrix(int n, const double *a, double *x, int *need) {
   constexpr int ROWS = 64 * RW;
