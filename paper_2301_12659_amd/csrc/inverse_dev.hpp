@@ -269,8 +269,10 @@ __device__ __forceinline__ double residual_entry(int n, int v, int parts, bool d
 }
 
 // What a residual of `limbs` limbs cannot tell from zero, relative to the size of
-// its terms: an omega below it does not measure the contraction to the next.
-__device__ __forceinline__ double refine_floor(int limbs) { return ldexp(1.0, 16 - 53 * limbs); }
+// its terms: neither an omega below it measures the contraction to the next, nor
+// the next one the contraction from it.  (The rounding errors of level sums grow
+// from level to level: 2^-401 in 8 limbs with n = 130.)
+__device__ __forceinline__ double refine_floor(int limbs) { return ldexp(1.0, 16 - 51 * limbs); }
 
 // Row j of M, y, by iterative refinement y += (e_j - y A_0) X from
 // the inverse X (x0) in doubles.  Rows, not columns: lane v then reads column v
@@ -282,7 +284,9 @@ __device__ __forceinline__ double refine_floor(int limbs) { return ldexp(1.0, 16
 // precision: the correction just added was then the last one that counts.  (The
 // first omega alone says nothing of the contraction: it is about 2^-53
 // whatever the conditioning.  Ended on it, double-double rows were up to five
-// digits behind the factorization at cond(A_0) = 1e12.)  Early passes form the
+// digits behind the factorization at cond(A_0) = 1e12.)  An omega below the floor
+// of the residual before is that one's rounding error and no contraction: counted
+// as one, octo-double rows went on until they did not contract any more.  Early passes form the
 // residual with only the limbs they need; the last one takes one limb more than
 // the working precision (and y carries one more), so that M is A_0^{-1} rounded
 // to L limbs, without the rounding errors of a residual at L limbs, which
@@ -315,7 +319,7 @@ __device__ void refine_row(int n, int S, int j, const double *a, const double *x
   int limbs = 1;  // of the residual before
   for (int pass = 0;; ++pass) {
     // the last pass that counts, if it contracts as those before it
-    const bool last = pass > 0 && prev * rho * rho * 1024.0 <= done;
+    const bool last = pass > 0 && (prev * rho * rho * 1024.0 <= done || prev <= refine_floor(L));
     double om = 0.0, e = 0.0, t = 0.0;
     // level sums of this wavefront's part of the terms at P limbs, then the
     // entries by the wavefronts of part 0
@@ -364,9 +368,8 @@ __device__ void refine_row(int n, int S, int j, const double *a, const double *x
       for (int l = 0; l < LX; ++l) ys[l * n + v] = s[l];
     }
     __syncthreads();
-    const double ratio = om / fmax(prev, refine_floor(limbs));
-    if (last && om * fmax(fmax(rho, ratio), 0x1p-53) * 64.0 <= done) break;
-    rho = fmax(rho, ratio);
+    if (pass == 0 || !(om <= refine_floor(limbs))) rho = fmax(rho, om / fmax(prev, refine_floor(limbs)));
+    if (last && om * fmax(rho, 0x1p-53) * 64.0 <= done) break;
     prev = om;
     limbs = pass == 0 ? 2 : last ? LX : L == 8 && pass <= 2 ? 4 : L;
     if (!(rho <= 0x1p-8) || pass >= 8 * L) {  // not contracting (or not finite)

@@ -31,7 +31,7 @@ __device__ bool refine_row_small(int n, int j, const double *as, const double *x
   double prev = 1.0, rho = 0.0;
   int limbs = 1;  // of the residual before
   for (int pass = 0;; ++pass) {
-    const bool last = pass > 0 && prev * rho * rho * 1024.0 <= done;
+    const bool last = pass > 0 && (prev * rho * rho * 1024.0 <= done || prev <= refine_floor(L));
     double e = 0.0, t = 0.0;
     auto form = [&](auto tag) {
       constexpr int P = decltype(tag)::value, LA = P > L ? L : P;
@@ -90,9 +90,8 @@ __device__ bool refine_row_small(int n, int j, const double *as, const double *x
     cv[0] = c;
     MD<LX>::add(y, cv, r);
     md::copy<LX>(r, y);
-    const double ratio = om / fmax(prev, refine_floor(limbs));
-    if (last && om * fmax(fmax(rho, ratio), 0x1p-53) * 64.0 <= done) break;
-    rho = fmax(rho, ratio);
+    if (pass == 0 || !(om <= refine_floor(limbs))) rho = fmax(rho, om / fmax(prev, refine_floor(limbs)));
+    if (last && om * fmax(rho, 0x1p-53) * 64.0 <= done) break;
     prev = om;
     limbs = pass == 0 ? 2 : last ? LX : L;
     if (!(rho <= 0x1p-8) || pass >= 8 * L) return false;  // not contracting (or not finite)
