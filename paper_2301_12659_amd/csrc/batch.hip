@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(64 * NW) batch_inv64_kernel(BatchArgs B, int l
   PathMeta pm;
   const PathSlot<L, Ls> w = block_path<L, Ls>(B, pm);
   if (pm.n <= lo || pm.n > NB * NW) return;
-  inv64_matrix<RW, NB, NW>(pm.n, w.qr, w.qt, path_need(w));
+  inv64_matrix<Ls, RW, NB, NW>(pm.n, w.qr, w.qt, path_need(w));
 }
 // (sizes lo < n <= hi; grid.y: rows)
 template <int L, int Ls>

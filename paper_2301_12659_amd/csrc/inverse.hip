@@ -11,26 +11,29 @@
 //
 // The refinement is taken only where it is as good as the factorization.
 // inv64_kernel raises *need when A_0 has no pivot, a non-finite entry or
-// ||A_0||_F ||X||_F >= 2^40, and refine_kernel when a row's residual does
+// ||A_0||_F ||X||_F >= 2^40, also once the scales of its rows and columns are taken
+// out (powers of two, exact), and refine_kernel when a row's residual does
 // not contract; the launches of the factorization that follow on the stream
-// return at once unless *need is set.  Below that bound no diagonal entry of
-// R can be under the singularity threshold of the factorization
-// (|R_ii| >= sigma_min >= 1/||X||_F, |R_jj| <= ||A_0||_F), so that the same
-// matrices are reported singular as by the factorization alone.  A matrix that
-// does not suit pays for the attempt: a step of one coefficient at cond(A_0) = 1e13
-// takes 288 us instead of 249 with the factorization alone (double double, n =
-// 64; 529 and 488 in quad double).  The bound is on A_0 as it is: rows of
-// scales 2^40 apart take that way, too, however well conditioned otherwise.
+// return at once unless *need is set.  No diagonal entry of R is then under the
+// singularity threshold of the factorization (|R_ii| >= sigma_min >= 1/||X||_F,
+// |R_jj| <= ||A_0||_F, and ||A_0||_F ||X||_F < 2^(53 L - 8) / n for a scaled
+// matrix, too), so that the same matrices are reported singular as by the
+// factorization alone.  A matrix that does not suit pays for the attempt: a step of
+// one coefficient at cond(A_0) = 1e13 takes 291 us instead of 250 with the
+// factorization alone (double double, n = 64; 533 and 488 in quad double).  One
+// whose rows differ in scale by 2^50 does not: the medium quad-double system, every
+// other polynomial times 2^-50, 462 us a step, 860 factorized after a first attempt
+// and 735 without.
 #include "inverse_dev.hpp"
 #include "kernels.hpp"
 
 namespace mdk {
 
-template <int RW, int NB, int NW>
+template <int L, int RW, int NB, int NW>
 __global__ void __launch_bounds__(64 * NW) inv64_kernel(int n, const double *a, double *x, int *need) {
   // on the chain of the step, beside the evaluation: raised issue priority
   __builtin_amdgcn_s_setprio(3);
-  inv64_matrix<RW, NB, NW>(n, a, x, need);
+  inv64_matrix<L, RW, NB, NW>(n, a, x, need);
 }
 
 template <int L>
@@ -56,16 +59,26 @@ static void launch_refine(int n, const double *a, const double *x0, double *M, i
   hipLaunchKernelGGL(refine_kernel<L>, dim3(n), dim3(64 * blocks * S), refine_lds<L>(n, S), st, n, S, a, x0, M, need);
 }
 
+template <int L>
+static void launch_inv64(int n, const double *a, double *x0, int *need, hipStream_t st) {
+  if (n <= 8) hipLaunchKernelGGL((inv64_kernel<L, 1, 8, 1>), dim3(1), dim3(64), 0, st, n, a, x0, need);
+  else if (n <= 32) hipLaunchKernelGGL((inv64_kernel<L, 1, 8, 4>), dim3(1), dim3(256), 0, st, n, a, x0, need);
+  else if (n <= 64) hipLaunchKernelGGL((inv64_kernel<L, 1, 8, 8>), dim3(1), dim3(512), 0, st, n, a, x0, need);
+  else if (n <= 128) hipLaunchKernelGGL((inv64_kernel<L, 2, 8, 16>), dim3(1), dim3(1024), 0, st, n, a, x0, need);
+  else if constexpr (L > 2)  // (inverse_refined)
+    hipLaunchKernelGGL((inv64_kernel<L, 3, 12, 16>), dim3(1), dim3(1024), 0, st, n, a, x0, need);
+}
+
 hipError_t launch_inverse(int L, int n, const double *a, double *x0, double *M, int *need, hipStream_t st) {
   if (!inverse_refined(L, n)) return hipErrorInvalidValue;
-  if (n <= 8) hipLaunchKernelGGL((inv64_kernel<1, 8, 1>), dim3(1), dim3(64), 0, st, n, a, x0, need);
-  else if (n <= 32) hipLaunchKernelGGL((inv64_kernel<1, 8, 4>), dim3(1), dim3(256), 0, st, n, a, x0, need);
-  else if (n <= 64) hipLaunchKernelGGL((inv64_kernel<1, 8, 8>), dim3(1), dim3(512), 0, st, n, a, x0, need);
-  else if (n <= 128) hipLaunchKernelGGL((inv64_kernel<2, 8, 16>), dim3(1), dim3(1024), 0, st, n, a, x0, need);
-  else hipLaunchKernelGGL((inv64_kernel<3, 12, 16>), dim3(1), dim3(1024), 0, st, n, a, x0, need);
-  if (L == 2) launch_refine<2>(n, a, x0, M, need, st);
-  else if (L == 4) launch_refine<4>(n, a, x0, M, need, st);
-  else launch_refine<8>(n, a, x0, M, need, st);
+  auto run = [&](auto tag) {
+    constexpr int LL = decltype(tag)::value;
+    launch_inv64<LL>(n, a, x0, need, st);
+    launch_refine<LL>(n, a, x0, M, need, st);
+  };
+  if (L == 2) run(std::integral_constant<int, 2>{});
+  else if (L == 4) run(std::integral_constant<int, 4>{});
+  else run(std::integral_constant<int, 8>{});
   return hipGetLastError();
 }
 

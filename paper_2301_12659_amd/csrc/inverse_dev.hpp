@@ -38,6 +38,33 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
   return max(max(a, b), max(c, d));
 }
 
+// Exponents of the largest entries of a's rows (re) and, these taken out, of its
+// columns (ce), by one workgroup of at least n threads; whether they differ by more
+// than a few powers of two (uniform).
+__device__ inline bool scale_exponents(int n, const double *a, int *re, int *ce) {
+  constexpr int NONE = -(1 << 20);
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nw = blockDim.x >> 6;
+  auto exponent = [&](int i, int j) {
+    const double e = fabs(a[(size_t)i * n + j]);
+    return e > 0.0 ? __builtin_amdgcn_frexp_exp(e) : NONE;
+  };
+  if (tid < n) ce[tid] = NONE;
+  for (int i = w; i < n; i += nw) {
+    int m = NONE;
+    for (int j = lane; j < n; j += 64) m = max(m, exponent(i, j));
+    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off, 64));
+    if (lane == 0) re[i] = m;
+  }
+  __syncthreads();
+  for (int j = lane; j < n; j += 64) {
+    int m = NONE;
+    for (int i = w; i < n; i += nw) m = max(m, exponent(i, j) - re[i]);
+    atomicMax(&ce[j], m);
+  }
+  __syncthreads();
+  return __syncthreads_or(tid < n && (abs(re[tid] - re[0]) >= 4 || abs(ce[tid] - ce[0]) >= 4)) != 0;
+}
+
 // In-place Gauss-Jordan inversion of the leading limbs of a ([n][n]
 // row-major) by one workgroup of NW wavefronts, the matrix in registers: wavefront
 // w owns the panel of NB columns from NB w on, lane i the rows i + 64 s of
@@ -53,162 +80,198 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
 // lanes, lane reads, one division), where one column per barrier with the rows
 // spread over the wavefronts took 1.1 us (n = 64); with three rows a lane it is
 // 7.5 us (n = 160: 1.2 ms), the factors read from LDS for every entry.
-template <int RW, int NB, int NW>
+//
+// *need becomes 1 where a is not regular or ||a||_F ||x||_F is 2^40 or more, else
+// 0.  Before it says so, a matrix whose rows or columns differ in scale is inverted
+// once more with their powers of two taken out, which the refinement does not
+// notice: it is exact in them.  Then the bound is on the scaled matrix, and on a
+// itself the one below which the factorization to L limbs would not have found
+// a singular (inverse.hip).
+template <int L, int RW, int NB, int NW>
 __device__ void inv64_matrix(int n, const double *a, double *x, int *need) {
   constexpr int ROWS = 64 * RW;
   __shared__ double panel[2][NB][ROWS];
   __shared__ int perm[NB * NW], where[ROWS], bad[2];
   __shared__ double red[2][NW];
+  __shared__ int re[ROWS], ce[ROWS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c0 = w * NB;
-  double v[RW][NB];
-  double na = 0.0;
-#pragma unroll
-  for (int s = 0; s < RW; ++s)
-#pragma unroll
-    for (int c = 0; c < NB; ++c) {
-      const int i = lane + 64 * s, j = c0 + c;
-      v[s][c] = (i < n && j < n) ? a[(size_t)i * n + j] : 0.0;
-      na = __builtin_fma(v[s][c], v[s][c], na);
-    }
-  bool used[RW];  // own rows that were pivots
-#pragma unroll
-  for (int s = 0; s < RW; ++s) used[s] = lane + 64 * s >= n;
-  // entry of column c in row p (uniform), uniform
-  auto entry = [&](int c, int p) {
-    double e = v[0][c];
-#pragma unroll
-    for (int s = 1; s < RW; ++s) e = (p >> 6) == s ? v[s][c] : e;
-    return lane_f64(e, p & 63);
-  };
-  __syncthreads();
-  const int panels = (n + NB - 1) / NB;
-  for (int q = 0; q < panels; ++q) {
-    const int buf = q & 1;
-    // the next panel's owner is on the chain, the other updates beside it not
-    if (w == q + 1 || w == q) __builtin_amdgcn_s_setprio(3);
-    else __builtin_amdgcn_s_setprio(1);
-    if (w == q) {
-      bool ok = true;
-#pragma unroll
-      for (int m = 0; m < NB; ++m) {
-        if (c0 + m < n) {
-          unsigned key = 0;
-#pragma unroll
-          for (int s = 0; s < RW; ++s) {
-            const unsigned h = (unsigned)(__double_as_longlong(v[s][m]) >> 32) & 0x7fffff00u;
-            const unsigned ks = used[s] || h == 0 ? 0u : (h | (unsigned)(lane + 64 * s));
-            key = max(key, ks);
-          }
-          key = wave_max_u32(key);
-          ok = ok && key != 0;
-          const int p = (int)(key & 255u);
-          double row[NB];
-#pragma unroll
-          for (int c = 0; c < NB; ++c) row[c] = entry(c, p);
-          const double inv = 1.0 / row[m];
-#pragma unroll
-          for (int c = 0; c < NB; ++c) row[c] *= inv;
-          row[m] = inv;
-#pragma unroll
-          for (int s = 0; s < RW; ++s) {
-            const bool piv = lane + 64 * s == p;
-            const double f = -v[s][m];
-            v[s][m] = 0.0;
-#pragma unroll
-            for (int c = 0; c < NB; ++c) v[s][c] = piv ? row[c] : __builtin_fma(f, row[c], v[s][c]);
-            used[s] = used[s] || piv;
-          }
-          if (lane == 0) {
-            perm[c0 + m] = p;
-            where[p] = c0 + m;
-          }
-        }
-      }
-      if (lane == 0) bad[buf] = ok ? 0 : 1;
-#pragma unroll
-      for (int s = 0; s < RW; ++s)
-#pragma unroll
-        for (int m = 0; m < NB; ++m) panel[buf][m][lane + 64 * s] = v[s][m];
+  // product of the squares of two norms, summed over the workgroup (uniform; the
+  // last bits of the sums are the same in every wavefront)
+  auto norms = [&](double na, double nx) {
+    na = team_sum_f64(na, 64);
+    nx = team_sum_f64(nx, 64);
+    if (lane == 0) {
+      red[0][w] = na;
+      red[1][w] = nx;
     }
     __syncthreads();
-    // no pivot: the same decision in every wavefront, since the word alternates
-    // like the panels (the next owner may be done before the last wavefront
-    // reads this one; the one after next waits for the next barrier)
-    if (bad[buf]) {
-      if (tid == 0) *need = 1;
-      return;
-    }
-    if (w != q && c0 < n) {
-      int pr[NB];
-      double wt[RW][NB];
-      const int width = min(NB, n - q * NB);
-#pragma unroll
-      for (int m = 0; m < NB; ++m) {
-        pr[m] = m < width ? __builtin_amdgcn_readfirstlane(perm[q * NB + m]) : 0;
-#pragma unroll
-        for (int s = 0; s < RW; ++s)
-          wt[s][m] = RW < 3 && m < width ? panel[buf][m][lane + 64 * s] : 0.0;
-      }
-      bool in[RW];
-#pragma unroll
-      for (int s = 0; s < RW; ++s) {
-        in[s] = false;
-#pragma unroll
-        for (int m = 0; m < NB; ++m) in[s] = in[s] || (m < width && lane + 64 * s == pr[m]);
-        used[s] = used[s] || in[s];
-      }
-#pragma unroll
-      for (int c = 0; c < NB; ++c) {
-        double y[NB];
-#pragma unroll
-        for (int m = 0; m < NB; ++m) y[m] = entry(c, pr[m]);
-#pragma unroll
-        for (int s = 0; s < RW; ++s) {
-          double t = in[s] ? 0.0 : v[s][c];
-          if constexpr (RW < 3) {
-#pragma unroll
-            for (int m = 0; m < NB; ++m) t = __builtin_fma(wt[s][m], y[m], t);
-          } else {  // W stays in LDS: with three rows a lane its registers are full
-#pragma unroll
-            for (int m = 0; m < NB; ++m)
-              if (m < width) t = __builtin_fma(panel[buf][m][lane + 64 * s], y[m], t);
-          }
-          v[s][c] = t;
-        }
-        if constexpr (RW == 3) asm volatile("" ::: "memory");
-      }
-    }
-  }
-  double nx = 0.0;
-#pragma unroll
-  for (int s = 0; s < RW; ++s)
-#pragma unroll
-    for (int c = 0; c < NB; ++c) nx = __builtin_fma(v[s][c], v[s][c], nx);
-  na = team_sum_f64(na, 64);
-  nx = team_sum_f64(nx, 64);
-  if (lane == 0) {
-    red[0][w] = na;
-    red[1][w] = nx;
-  }
-  __syncthreads();
-  if (tid == 0) {
     double sa = 0.0, sx = 0.0;
     for (int q = 0; q < NW; ++q) {
       sa += red[0][q];
       sx += red[1][q];
     }
-    *need = sa * sx < 0x1p80 ? 0 : 1;  // also when a norm is not finite
-  }
-  // entry (k, perm[m]) of the inverse is in row perm[k], column m
+    return sa * sx;
+  };
+  double v[RW][NB];
+  for (bool scaled = false;; scaled = true) {
+    double na = 0.0;
 #pragma unroll
-  for (int s = 0; s < RW; ++s)
+    for (int s = 0; s < RW; ++s)
 #pragma unroll
-    for (int c = 0; c < NB; ++c) {
-      const int i = lane + 64 * s, j = c0 + c;
-      if (i < n && j < n) x[(size_t)where[i] * n + perm[j]] = v[s][c];
+      for (int c = 0; c < NB; ++c) {
+        const int i = lane + 64 * s, j = c0 + c;
+        v[s][c] = (i < n && j < n) ? a[(size_t)i * n + j] : 0.0;
+        if (scaled && i < n && j < n) v[s][c] = ldexp(v[s][c], -(re[i] + ce[j]));
+        na = __builtin_fma(v[s][c], v[s][c], na);
+      }
+    bool used[RW];  // own rows that were pivots
+#pragma unroll
+    for (int s = 0; s < RW; ++s) used[s] = lane + 64 * s >= n;
+    // entry of column c in row p (uniform), uniform
+    auto entry = [&](int c, int p) {
+      double e = v[0][c];
+#pragma unroll
+      for (int s = 1; s < RW; ++s) e = (p >> 6) == s ? v[s][c] : e;
+      return lane_f64(e, p & 63);
+    };
+    __syncthreads();
+    bool regular = true;
+    const int panels = (n + NB - 1) / NB;
+    for (int q = 0; q < panels; ++q) {
+      const int buf = q & 1;
+      // the next panel's owner is on the chain, the other updates beside it not
+      if (w == q + 1 || w == q) __builtin_amdgcn_s_setprio(3);
+      else __builtin_amdgcn_s_setprio(1);
+      if (w == q) {
+        bool ok = true;
+#pragma unroll
+        for (int m = 0; m < NB; ++m) {
+          if (c0 + m < n) {
+            unsigned key = 0;
+#pragma unroll
+            for (int s = 0; s < RW; ++s) {
+              const unsigned h = (unsigned)(__double_as_longlong(v[s][m]) >> 32) & 0x7fffff00u;
+              const unsigned ks = used[s] || h == 0 ? 0u : (h | (unsigned)(lane + 64 * s));
+              key = max(key, ks);
+            }
+            key = wave_max_u32(key);
+            ok = ok && key != 0;
+            const int p = (int)(key & 255u);
+            double row[NB];
+#pragma unroll
+            for (int c = 0; c < NB; ++c) row[c] = entry(c, p);
+            const double inv = 1.0 / row[m];
+#pragma unroll
+            for (int c = 0; c < NB; ++c) row[c] *= inv;
+            row[m] = inv;
+#pragma unroll
+            for (int s = 0; s < RW; ++s) {
+              const bool piv = lane + 64 * s == p;
+              const double f = -v[s][m];
+              v[s][m] = 0.0;
+#pragma unroll
+              for (int c = 0; c < NB; ++c) v[s][c] = piv ? row[c] : __builtin_fma(f, row[c], v[s][c]);
+              used[s] = used[s] || piv;
+            }
+            if (lane == 0) {
+              perm[c0 + m] = p;
+              where[p] = c0 + m;
+            }
+          }
+        }
+        if (lane == 0) bad[buf] = ok ? 0 : 1;
+#pragma unroll
+        for (int s = 0; s < RW; ++s)
+#pragma unroll
+          for (int m = 0; m < NB; ++m) panel[buf][m][lane + 64 * s] = v[s][m];
+      }
+      __syncthreads();
+      // no pivot: the same decision in every wavefront, since the word alternates
+      // like the panels (the next owner may be done before the last wavefront
+      // reads this one; the one after next waits for the next barrier)
+      if (bad[buf]) {
+        regular = false;
+        break;
+      }
+      if (w != q && c0 < n) {
+        int pr[NB];
+        double wt[RW][NB];
+        const int width = min(NB, n - q * NB);
+#pragma unroll
+        for (int m = 0; m < NB; ++m) {
+          pr[m] = m < width ? __builtin_amdgcn_readfirstlane(perm[q * NB + m]) : 0;
+#pragma unroll
+          for (int s = 0; s < RW; ++s)
+            wt[s][m] = RW < 3 && m < width ? panel[buf][m][lane + 64 * s] : 0.0;
+        }
+        bool in[RW];
+#pragma unroll
+        for (int s = 0; s < RW; ++s) {
+          in[s] = false;
+#pragma unroll
+          for (int m = 0; m < NB; ++m) in[s] = in[s] || (m < width && lane + 64 * s == pr[m]);
+          used[s] = used[s] || in[s];
+        }
+#pragma unroll
+        for (int c = 0; c < NB; ++c) {
+          double y[NB];
+#pragma unroll
+          for (int m = 0; m < NB; ++m) y[m] = entry(c, pr[m]);
+#pragma unroll
+          for (int s = 0; s < RW; ++s) {
+            double t = in[s] ? 0.0 : v[s][c];
+            if constexpr (RW < 3) {
+#pragma unroll
+              for (int m = 0; m < NB; ++m) t = __builtin_fma(wt[s][m], y[m], t);
+            } else {  // W stays in LDS: with three rows a lane its registers are full
+#pragma unroll
+              for (int m = 0; m < NB; ++m)
+                if (m < width) t = __builtin_fma(panel[buf][m][lane + 64 * s], y[m], t);
+            }
+            v[s][c] = t;
+          }
+          if constexpr (RW == 3) asm volatile("" ::: "memory");
+        }
+      }
     }
+    bool good = false;
+    if (regular) {
+      double nx = 0.0;
+#pragma unroll
+      for (int s = 0; s < RW; ++s)
+#pragma unroll
+        for (int c = 0; c < NB; ++c) nx = __builtin_fma(v[s][c], v[s][c], nx);
+      good = norms(na, nx) < 0x1p80;  // not when a norm is not finite
+      // entry (k, perm[m]) of the inverse is in row perm[k], column m
+      na = nx = 0.0;
+#pragma unroll
+      for (int s = 0; s < RW; ++s)
+#pragma unroll
+        for (int c = 0; c < NB; ++c) {
+          const int i = lane + 64 * s, j = c0 + c;
+          if (i < n && j < n) {
+            double e = v[s][c];
+            if (scaled) {
+              e = ldexp(e, -(ce[where[i]] + re[perm[j]]));
+              const double b = a[(size_t)i * n + j];
+              na = __builtin_fma(b, b, na);
+              nx = __builtin_fma(e, e, nx);
+            }
+            x[(size_t)where[i] * n + perm[j]] = e;
+          }
+        }
+      if (scaled) {
+        __syncthreads();  // (red was read)
+        good = good && norms(na, nx) < ldexp(1.0, 106 * L - 16) / ((double)n * n);
+      }
+    }
+    if (good || scaled || !scale_exponents(n, a, re, ce)) {
+      if (tid == 0) *need = good ? 0 : 1;
+      return;
+    }
+  }
 }
 
 // Lane-wise level sums of the terms i0 <= i < i1 of column v of -y A_0 (y

@@ -140,7 +140,7 @@ __global__ void __launch_bounds__(PREPASS_NT) prepass_small_kernel(EvalArgs a, c
     for (int l = 0; l < L; ++l) as[l * nn + ij] = acc[l];
   }
   __syncthreads();
-  inv64_matrix<1, 8, PREPASS_NT / 64>(n, as, xs, &need);
+  inv64_matrix<L, 1, 8, PREPASS_NT / 64>(n, as, xs, &need);
   __syncthreads();
   if (!need) {
     __syncthreads();  // (need was read)
